@@ -272,7 +272,8 @@ typedef struct fp6_plan_info {
     int waves;              /* wavefronts per workgroup                                                */
     int depth;              /* tiles (decode) or stages (gemm) in the prefetch ring                    */
     int half_tiles;         /* decode: 1 = workgroups own 32 channels                                   */
-    int meeting;            /* how K-slices are added: 0 none, 1 arrival counter, 2 pairwise slots      */
+    int meeting;            /* how K-slices are added: 0 none, 1 through partial sums (by the last workgroup to arrive
+                               or, gemm family with much to add, by a second launch), 2 pairwise slots  */
     int64_t workgroups;     /* launch grid                                                             */
     size_t workspace_bytes; /* what the matching *_workspace_bytes call returns                        */
 } fp6_plan_info;

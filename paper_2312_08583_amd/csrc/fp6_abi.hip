@@ -309,6 +309,13 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
         p.pairwise = variant == FP6_VARIANT_DECODE && fits && (hint_meet ? hint_meet == 2 : p.split_k == 2);
         if (!p.pairwise) {
             p.counters = (int)tiles;
+            // The last arriver of a block of Y reads all its slices by itself, at the 40 GB/s of one compute unit; a second
+            // launch spreads that over the chip and costs about 3 us more.  Measured, us (last arriver / second launch):
+            // 100 x 8192 x 28672 in eight slices of 112 KB 81 / 63; 100 x 5120 x 5120, five of 56 KB 20.4 / 18.2;
+            // 48 x 13824 x 5120, four of 48 KB 22.3 / 21.2; 64 x 5120 x 5120, five of 32 KB 15.4 / 17.0; 512 x 1024 x 8192,
+            // four of 32 KB 22.2 / 25.1.  Two slices: the last arriver reads one only (128 KB each: 112 / 121).
+            const int64_t rows = M < p.block_m ? (M + 15) / 16 * 16 : p.block_m;
+            p.second_launch = variant == FP6_VARIANT_GEMM && p.split_k > 2 && p.split_k * rows * 256 * p.gbn >= 192 * 1024;
             p.partial_bytes = (size_t)p.split_k * (size_t)tiles * (size_t)regs_per_tile * 16u;
         }
     }

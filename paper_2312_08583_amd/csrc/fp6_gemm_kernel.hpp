@@ -93,7 +93,7 @@ template <int BM, int D, int WN, int DQ, bool FGQ, int FMT, int GBN, int KW = 1,
 __global__ __launch_bounds__(GBN / WN * KW * 64, (GBN == 4 && KW == 1) ? 2 : 1) void gemm_kernel(
     const uint16_t* __restrict__ X, int M, const u32x4* __restrict__ hi, const u32x4* __restrict__ lo,
     const uint16_t* __restrict__ scales, int N, int K, uint16_t* __restrict__ Y,
-    float4v* __restrict__ partials, uint32_t* __restrict__ counters, int split_k, int gshift)
+    float4v* __restrict__ partials, uint32_t* __restrict__ counters, int split_k, int gshift, int second_launch)
 {
     static_assert(!FGQ || (WN == 1 && BM <= 64 && KW == 1), "fine-grained scales: two accumulators must fit the register file");
     static_assert(KW == 1 || (KW == 2 && WN == 1), "K-ways inside the workgroup: one or two");
@@ -347,10 +347,13 @@ __global__ __launch_bounds__(GBN / WN * KW * 64, (GBN == 4 && KW == 1) ? 2 : 1) 
         if (holds_y) {
             __amdgpu_buffer_rsrc_t win = partial_window(partials + ((size_t)s * ntiles + tile) * kTileRegs, kTileRegs * 16);
 #pragma unroll
-            for (int a = 0; a < MT; a++)
+            for (int a = 0; a < MT; a++) {
+                if (m0 + a * 16 >= M) break;              // rows past M: nobody reads them
 #pragma unroll
                 for (int t = 0; t < NT; t++) store_partial(win, (a * NT + t) * OUT_THREADS + tid2, acc[a][t]);
+            }
         }
+        if (second_launch) return;                        // add_slices_kernel does the rest
         if (!arrive_last(&counters[tile * kCounterStride], (uint32_t)split_k)) return;
         if (!holds_y) return;
         // Two slices: the one that arrives last adds the other's sums to its own, which it still holds - a + b
@@ -424,6 +427,42 @@ __global__ __launch_bounds__(GBN / WN * KW * 64, (GBN == 4 && KW == 1) ? 2 : 1) 
     }
 }
 
+// The second launch of a split layer: adds the slices (in slice order) and applies the epilogue.  A wavefront takes four rows
+// of one 64-channel block, 16 lanes a row, so that Y is written as whole 128-byte pieces.  GBN and BM are those of the launch
+// that wrote the partial sums (a block of Y holds them as [row block a][16-channel block t][thread]).
+template <bool FGQ, int FMT, int DQ>
+__global__ __launch_bounds__(256) void add_slices_kernel(const float4v* __restrict__ partials, const uint16_t* __restrict__ scales,
+                                                         int M, int N, int bm, int gbn, int split_k, uint16_t* __restrict__ Y)
+{
+    const int lane = threadIdx.x & 63;
+    const int nblocks = N / kTile;
+    const unsigned item = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int nb = (int)(item % (unsigned)nblocks), m = (int)(item / (unsigned)nblocks) * 4 + (lane >> 4);
+    if (m >= M) return;
+    const int t = (lane >> 2) & 3, g = lane & 3;
+    const int mblk = (M + bm - 1) / bm, nblk = (nblocks + gbn - 1) / gbn;
+    const int mb = m / bm, a = (m % bm) >> 4, i = m & 15;
+    const size_t tile_regs = (size_t)bm * gbn * 16;
+    const size_t slice = tile_regs * mblk * nblk;
+    const float4v* p = partials + ((size_t)(nb / gbn) * mblk + mb) * tile_regs + (size_t)(a * 4 + t) * (gbn * 64) + (nb % gbn) * 64 + g * 16 + i;
+    const int n = nb * kTile + t * 16 + g * 4;
+    half4 sc = half4{1, 1, 1, 1};          // fine-grained scales were applied block by block
+    if (!FGQ) sc = *reinterpret_cast<const half4*>(scales + n);
+    float4v sum = float4v{0.f, 0.f, 0.f, 0.f};
+    for (int s0 = 0; s0 < split_k; s0 += 8) {          // eight loads in flight
+        float4v v[8];
+#pragma unroll
+        for (int u = 0; u < 8; u++) v[u] = p[(size_t)min(s0 + u, split_k - 1) * slice];
+#pragma unroll
+        for (int u = 0; u < 8; u++)
+            if (s0 + u < split_k) sum += v[u];
+    }
+    float yv[4];
+#pragma unroll
+    for (int r = 0; r < 4; r++) yv[r] = sum[r] * ((float)sc[r] * kUnshift<DQ, FMT>);
+    *reinterpret_cast<half4*>(Y + (size_t)m * N + n) = to_out4<FMT>(yv);
+}
+
 template <int BM, int D, int WN, int DQ = kBiasShift, bool FGQ = false, int FMT = kE3M2, int GBN = 8, int KW = 1, int DX = D>
 static hipError_t launch_gemm_t(const LinearPlan& p, const uint16_t* X, int64_t M, const void* hi, const void* lo,
                                 const uint16_t* scales, int64_t N, int64_t K, uint16_t* Y, void* workspace,
@@ -434,7 +473,14 @@ static hipError_t launch_gemm_t(const LinearPlan& p, const uint16_t* X, int64_t 
     const int64_t mblk = (M + BM - 1) / BM, nblk = (N / kTile + GBN - 1) / GBN;
     const unsigned grid = (unsigned)(mblk * ((nblk * p.split_k + 7) / 8 * 8));   // padded: see the id mapping
     hipLaunchKernelGGL((gemm_kernel<BM, D, WN, DQ, FGQ, FMT, GBN, KW, DX>), dim3(grid), dim3(GBN / WN * KW * 64), 0, stream, X, (int)M,
-                       (const u32x4*)hi, (const u32x4*)lo, scales, (int)N, (int)K, Y, partials, counters, p.split_k, p.gshift);
+                       (const u32x4*)hi, (const u32x4*)lo, scales, (int)N, (int)K, Y, partials, counters, p.split_k, p.gshift, p.second_launch);
+    if (p.second_launch) {
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        const int64_t items = (M + 3) / 4 * (N / kTile);
+        hipLaunchKernelGGL((add_slices_kernel<FGQ, FMT, DQ>), dim3((unsigned)((items + 3) / 4)), dim3(256), 0, stream, partials, scales,
+                           (int)M, (int)N, BM, GBN, p.split_k, Y);
+    }
     return hipGetLastError();
 }
 
