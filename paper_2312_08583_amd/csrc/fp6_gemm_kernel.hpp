@@ -114,10 +114,14 @@ __global__ __launch_bounds__(GBN / WN * KW * 64, (GBN == 4 && KW == 1) ? 2 : 1) 
     constexpr int kTileRegs = MT * NT * OUT_THREADS;    // float4 per output tile
     constexpr int kSumBytes = KW > 1 ? kTileRegs * 16 : 0;        // LDS for adding the two K-ways
     constexpr int kSmemBytes = kRingBytes > kSumBytes ? kRingBytes : kSumBytes;
-    // loads that may still be in flight when a step starts: everything issued after the step's activations
-    // (the rest of that step's loads and DX - 2 whole steps) and after its planes (D - 2 whole steps)
-    constexpr int kInFlight = ((DX - 2) * kLoads + 3 * WN + (FGQ ? 1 : 0)) < ((D - 2) * kLoads)
-                                  ? ((DX - 2) * kLoads + 3 * WN + (FGQ ? 1 : 0)) : ((D - 2) * kLoads);
+    // loads that may still be in flight at the barrier of a step, where the next step's stage has to be there: everything
+    // issued after that stage's activations (the rest of that call's loads and DX - 2 whole calls) and after its planes
+    // (D - 2 whole calls); before the first step (kInFlight0) one call more
+    constexpr int kAfterX = 3 * WN + (FGQ ? 1 : 0);
+    constexpr int kInFlight = (DX - 2) * kLoads + kAfterX < (D - 2) * kLoads ? (DX - 2) * kLoads + kAfterX : (D - 2) * kLoads;
+    constexpr int kInFlight0 = (DX - 1) * kLoads + kAfterX < (D - 1) * kLoads ? (DX - 1) * kLoads + kAfterX : (D - 1) * kLoads;
+    // whole operands of the next step are held in registers beside this step's where they fit (see step() below)
+    constexpr bool kWhole = MT * (FGQ ? 2 : 1) <= 4;
     __shared__ __align__(16) unsigned char smem[kSmemBytes];
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -210,95 +214,155 @@ __global__ __launch_bounds__(GBN / WN * KW * 64, (GBN == 4 && KW == 1) ? 2 : 1) 
             if (FGQ) part[a][t] = float4v{0.f, 0.f, 0.f, 0.f};
         }
 
-    // prologue: the steps 0 .. D-2 of the planes; their activations only as far as the shorter ring reaches
-    // (a call always issues kLoads loads: a slot that is not due yet fetches what step 0 needs once more)
+    // prologue: the steps 0 .. D-1 of the planes; their activations as far as the shorter ring reaches, the step 0
+    // ones several times, and first (a call always issues kLoads loads)
 #pragma unroll
-    for (int u = 0; u < D - 1; u++) {
-        const int ux = u < DX - 1 ? u : 0;
+    for (int u = 0; u < D; u++) {
+        const int ux = u < D - DX ? 0 : u - (D - DX);
         issue(min(kt_begin + ux * KW, kt_last), ux, min(kt_begin + u * KW, kt_last), u);
     }
 
-    // One step (KW k tiles).  Its planes were issued D-1 steps ago, its activations DX-1 steps ago; kInFlight younger
-    // loads may stay in flight.  The stage numbers are compile-time constants (the loop below is unrolled over a
-    // whole period of both rings), so every LDS address is a register plus an immediate - a ring indexed at run
-    // time measured 10-20% slower.
-    auto step = [&](int kt, int ux, int uw) {
-        wait_vmcnt<kInFlight>();
-        __syncthreads();          // everyone's DMA landed; everyone is done with the stages refilled next
-        issue(min(kt + (DX - 1) * KW, kt_last), (ux + DX - 1) % DX, min(kt + (D - 1) * KW, kt_last), (uw + D - 1) % D);
-        const unsigned char* st = smem + ux * kXBytes;
+    // operand reads from a stage of the ring
+    auto read_x = [&](half8 (&x)[MT], int ux, int q) {
+        const unsigned char* st = smem + ux * kXBytes + (q ? xoff1 : xoff0);
+#pragma unroll
+        for (int a = 0; a < MT; a++) x[a] = *reinterpret_cast<const half8*>(st + a * 16 * (kTile * 2));
+    };
+    auto read_planes = [&](TileRaw (&r)[WN], int uw) {
         const unsigned char* wt = smem + kPlaneBase + uw * kPlaneBytes + wlds;
-        const unsigned char* sct = smem + kPlaneBase + uw * kPlaneBytes + kScaleOff;
-        TileRaw raw[WN];
 #pragma unroll
         for (int c = 0; c < WN; c++) {
-            raw[c].hi0 = *reinterpret_cast<const u32x4*>(wt + c * kWaveTileBytes + wlane);
-            raw[c].hi1 = *reinterpret_cast<const u32x4*>(wt + c * kWaveTileBytes + 1024 + wlane);
+            r[c].hi0 = *reinterpret_cast<const u32x4*>(wt + c * kWaveTileBytes + wlane);
+            r[c].hi1 = *reinterpret_cast<const u32x4*>(wt + c * kWaveTileBytes + 1024 + wlane);
             if (FMT != kE3M1) {
-                raw[c].lo = *reinterpret_cast<const u32x4*>(wt + c * kWaveTileBytes + 2048 + wlane);
+                r[c].lo = *reinterpret_cast<const u32x4*>(wt + c * kWaveTileBytes + 2048 + wlane);
             } else {
                 const u32x2 l = *reinterpret_cast<const u32x2*>(wt + c * kWaveTileBytes + 2048 + lane * 8);
-                raw[c].lo = u32x4{l.x, l.y, 0u, 0u};
+                r[c].lo = u32x4{l.x, l.y, 0u, 0u};
             }
         }
+    };
+    auto read_scales = [&](half4 (&h)[4], int uw) {
+        const unsigned char* sct = smem + kPlaneBase + uw * kPlaneBytes + kScaleOff + wave * 256;
 #pragma unroll
-        for (int q = 0; q < 2; q++) {
-            half8 xf[MT];
+        for (int t = 0; t < 4; t++) h[t] = *reinterpret_cast<const half4*>(sct + (t * 16 + g * 4) * 2);
+    };
+    // the products of one 32-wide k block
+    auto mac = [&](const TileRaw (&r)[WN], const half8 (&x)[MT], int q) {
 #pragma unroll
-            for (int a = 0; a < MT; a++) {
-                xf[a] = *reinterpret_cast<const half8*>(st + a * 16 * (kTile * 2) + (q ? xoff1 : xoff0));
-            }
+        for (int c = 0; c < WN; c++) {
+            half8 w4[4];
+            if (layout2(FMT)) unpack_kblock<DQ, FMT>(r[c], q, w4);     // all four fragments at once
 #pragma unroll
-            for (int c = 0; c < WN; c++) {
-                half8 w4[4];
-                if (layout2(FMT)) unpack_kblock<DQ, FMT>(raw[c], q, w4);     // all four fragments at once
+            for (int t4 = 0; t4 < 4; t4++) {
+                const int t = 4 * c + t4;
+                half8 w = layout2(FMT) ? w4[t4] : unpack_tile_fragment<DQ, FMT>(r[c], 2 * t4 + q);
 #pragma unroll
-                for (int t4 = 0; t4 < 4; t4++) {
-                    const int t = 4 * c + t4;
-                    half8 w = layout2(FMT) ? w4[t4] : unpack_tile_fragment<DQ, FMT>(raw[c], 2 * t4 + q);
-#pragma unroll
-                    for (int a = 0; a < MT; a++) {
-                        if (FGQ) part[a][t] = mfma16x16x32_of<FMT>(w, xf[a], part[a][t]);
-                        else acc[a][t] = mfma16x16x32_of<FMT>(w, xf[a], acc[a][t]);
-                    }
+                for (int a = 0; a < MT; a++) {
+                    if (FGQ) part[a][t] = mfma16x16x32_of<FMT>(w, x[a], part[a][t]);
+                    else acc[a][t] = mfma16x16x32_of<FMT>(w, x[a], acc[a][t]);
                 }
             }
         }
+    };
+
+    // Issue order.  Bias-shift FP6 at up to 64 rows: after the first fragment every MFMA (16 cycles in the matrix pipe) is
+    // followed by a few of the unpack VALU operations and, while there are any, one of the LDS reads, in its shadow.
+    // Plane layout 2 at 128 rows: an LDS read behind each of the first MFMAs (333 x 13824 x 5120 in bf16: 59.0 us, 63.0
+    // without).  The rest is left to the compiler: at 128 rows the first pattern spills, and the second costs bias-shift
+    // FP6 5 % (512 x 22016 x 8192: 170.0 us, 162.9 without).
+    auto hints = [&](int part_of_step) {
+#if FP6_GEMM_HINTS
+        if (kWhole && !FGQ && FMT == kE3M2 && DQ != kHalfMul) {
+            const int reads = part_of_step == 1 ? MT : 3 * WN + (kWhole ? 2 * MT : MT);
+            const int mfmas = NT * MT * (kWhole ? 2 : 1);
+            __builtin_amdgcn_sched_group_barrier(0x002, 15, 0);
+#pragma unroll
+            for (int n = 0; n < mfmas; n++) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                if (n < reads) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+            }
+        }
+        if (!kWhole && layout2(FMT)) {
+            const int reads = part_of_step == 1 ? MT : 3 * WN + MT;
+#pragma unroll
+            for (int n = 0; n < reads; n++) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            }
+        }
+#endif
+    };
+
+    TileRaw raw[WN];                  // planes of the current step
+    half8 x0[MT], x1[MT];             // its activations, k blocks 0 and 1 (x1 is loaded ahead only with kWhole)
+    half4 sc4[4];                     // FGQ: its scales
+    wait_vmcnt<kInFlight0>();
+    __syncthreads();
+    read_planes(raw, 0);
+    read_x(x0, 0, 0);
+    if (kWhole) read_x(x1, 0, 1);
+    if (FGQ && kWhole) read_scales(sc4, 0);
+
+    // One step (KW k tiles).  The wavefronts leave a barrier together; if they then had to read their operands from
+    // LDS, all of them would wait (88 KB at 128 rows and 128 B a cycle: 700 cycles beside 2048 of MFMAs per SIMD).  So a
+    // step starts with its operands in registers and reads the next step's behind the barrier, under its own MFMAs:
+    // with kWhole all of them; at 128 rows, where two sets don't fit the 256 registers, k block 1 is read under the
+    // MFMAs of block 0, the barrier comes between the blocks, and the next step's planes and block 0 are read under
+    // those of block 1.  Everyone's reads of the step's own stage are complete at the barrier, so that stage is refilled
+    // right behind it (planes D steps on, activations DX).  The stage numbers are compile-time constants (the loop below
+    // is unrolled over a whole period of both rings), so every LDS address is a register plus an immediate - a ring
+    // indexed at run time measured 10-20% slower.
+    auto step = [&](int kt, int ux, int uw) {
+        TileRaw raw_n[WN];
+        half8 x0_n[MT], x1_n[MT];
+        half4 sc_n[4];
+        if (!kWhole) {
+            read_x(x1, ux, 1);
+            if (FGQ) read_scales(sc4, uw);
+            mac(raw, x0, 0);
+            hints(0x1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        wait_vmcnt<kInFlight>();
+        __syncthreads();
+        issue(min(kt + DX * KW, kt_last), ux, min(kt + D * KW, kt_last), uw);
+        read_planes(raw_n, (uw + 1) % D);
+        read_x(x0_n, (ux + 1) % DX, 0);
+        if (kWhole) {
+            read_x(x1_n, (ux + 1) % DX, 1);
+            if (FGQ) read_scales(sc_n, (uw + 1) % D);
+            mac(raw, x0, 0);
+        }
+        mac(raw, x1, 1);
+        hints(0x2);
         if (FGQ) {
             // last tile of a block of K (or of this workgroup's K-slice): scale and accumulate
             if ((((kt + 1) >> gshift) << gshift) == kt + 1 || kt + 1 == kt_end) {
 #pragma unroll
                 for (int t = 0; t < NT; t++) {
-                    const half4 h = *reinterpret_cast<const half4*>(sct + wave * 256 + (t * 16 + g * 4) * 2);
 #pragma unroll
                     for (int a = 0; a < MT; a++) {
 #pragma unroll
-                        for (int r = 0; r < 4; r++) acc[a][t][r] += part[a][t][r] * (float)h[r];
+                        for (int r = 0; r < 4; r++) acc[a][t][r] += part[a][t][r] * (float)sc4[t][r];
                         part[a][t] = float4v{0.f, 0.f, 0.f, 0.f};
                     }
                 }
             }
         }
-        // Issue order.  The wavefronts of a SIMD leave the barrier together, so they cannot hide
-        // each other's unpack work; instead, after the first fragment, every MFMA (16 cycles in the
-        // matrix pipe) is followed by two (BM = 128) or four of the unpack VALU operations (in its
-        // shadow), and the LDS operand reads of the second k block are spread over the MFMAs of
-        // the first.
-#if FP6_GEMM_HINTS
-        // (tuned for the instruction mix of the FP6 bias-shift unpack; the other variants are left to the compiler,
-        // whose schedule needs fewer registers - and so are four-wavefront workgroups of 64 and 128 rows, whose two
-        // wavefronts on a SIMD come from different workgroups and do not leave a barrier together: 2 % faster unhinted)
-        if (!FGQ && FMT == kE3M2 && DQ != kHalfMul && (GBN * KW == 8 || BM == 32)) {
-        __builtin_amdgcn_sched_group_barrier(0x100, 3 * WN + MT, 0);     // planes + operands of k block 0
-        __builtin_amdgcn_sched_group_barrier(0x002, 15, 0);              // first fragment
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int n = 0; n < 2 * NT * MT; n++) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x002, MT >= 8 ? 2 : 4, 0);     // measured: 4 is 2-3 % ahead at BM <= 64, 9 % behind at 128
-            if (n % 2 == 0 && n >= NT * MT - 2 * MT && n < NT * MT) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        for (int c = 0; c < WN; c++) raw[c] = raw_n[c];
+#pragma unroll
+        for (int a = 0; a < MT; a++) {
+            x0[a] = x0_n[a];
+            if (kWhole) x1[a] = x1_n[a];
         }
+        if (FGQ && kWhole) {
+#pragma unroll
+            for (int t = 0; t < 4; t++) sc4[t] = sc_n[t];
         }
-#endif
     };
 
     constexpr int P = (D % DX == 0) ? D : D * DX;      // steps after which both rings are back at stage 0
