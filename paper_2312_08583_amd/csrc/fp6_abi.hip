@@ -57,6 +57,17 @@ static constexpr PlanModel kModel = {
     {0.77, 0.993, 1.417}, 0.57, 1.964, {0.528, 1.588, 4.681}, 2.774, 3.216, 4.529e6,
 };
 
+// K-slices of different lengths (by one k tile, or a pair).  K/64 of few divisors has no good even split (52 x 1600 x
+// 21696: 339 = 3 x 113 tiles), so slices that do not divide it are considered, and taken where the model's cost is this
+// fraction of the best even split's or less.  Plain FP6 keeps even slices where K/64 is a multiple of 16, and on layers
+// below 12 M weights unless K/64 is odd: the configured layers keep plans whose split_k a caller can also force.
+static constexpr double kUnevenGain = 0.93;
+static bool uneven_worth_a_look(bool plain, int64_t N, int64_t K)
+{
+    const int64_t ktiles = K / FP6_TILE;
+    return !plain || ktiles % 2 == 1 || (ktiles % 16 != 0 && N * K >= (int64_t)12 << 20);
+}
+
 // Number of K-slices for the decode family where the cost model below does not apply: layers of 256 channel
 // blocks or more at up to 16 rows of X (measured on MI355X at M = 1: no split from 384 blocks on; below, two
 // slices, which meet pairwise - cheaper than any larger number), eight-wavefront workgroups, very short K.
@@ -87,15 +98,18 @@ static int pick_decode_split(int64_t units, int64_t ktiles, int waves)
 // 35 GB/s x (16 / M)^0.57, the stream reaches 3.9 TB/s, and the meeting moves M / 16 times the bytes:
 // (0.5 + 0.09 per slice) x M / 16.  Mean distance from the best split of the sweep 1.5 % (the previous rule: 7 %).
 static void plan_small_decode(int64_t M, int64_t nblocks, int64_t ktiles, int tile_bytes, int waves, int forced_split,
-                              bool may_half, bool must_half, int* split_out, bool* half_out)
+                              bool may_half, bool must_half, bool even_only, int* split_out, bool* half_out)
 {
-    double best = 1e30;
+    double best = 1e30, best_uneven = 1e30;
+    int uneven_split = 0;
+    bool uneven_half = false;
     *split_out = forced_split ? forced_split : 1;
     *half_out = must_half;
     const double bytes = (double)nblocks * (double)ktiles * tile_bytes;
     for (int half = must_half ? 1 : 0; half <= (may_half || must_half ? 1 : 0); half++) {
         for (int64_t d = forced_split ? forced_split : 1; d <= (forced_split ? forced_split : 32) && d <= ktiles; d++) {
-            if (ktiles % d) continue;
+            const bool even = ktiles % d == 0;
+            if (!even && even_only) continue;
             if (d > 1 && ktiles / d < 2 * waves) break;       // every wavefront keeps at least two tiles
             const int64_t wgs = nblocks * d * (half ? 2 : 1);
             const double rounds = (double)((wgs + 255) / 256);
@@ -105,17 +119,27 @@ static void plan_small_decode(int64_t M, int64_t nblocks, int64_t ktiles, int ti
             // (FP5 half tiles fetch the 1-bit plane four bytes a lane: their lower rate separates 8192 x 8192, where they win, from 8192 x 22016, where they lose)
             const double rate = rows16 ? (half ? (tile_bytes == 3072 ? c.wg_half : c.wg_half_fp5) : c.wg_full)
                                        : c.wg_full * pow(16.0 / (double)M, c.wg_rows_exponent);
-            const double unit = rounds * (bytes / (double)wgs) / rate;
+            const double longest = (double)((ktiles + d - 1) / d * d) / (double)ktiles;     // the longest slice over the mean
+            const double unit = rounds * (bytes / (double)wgs) * longest / rate;
             const double meet = d == 1 ? 0.0
                                 : rows16 ? (d == 2 ? c.meet_pair : c.meet_base16 + c.meet_slice16 * (double)d)
                                          : (c.meet_base64 + c.meet_slice64 * (double)d) * (double)M / 16.0;
             const double cost = c.launch + (stream > unit ? stream : unit) + meet;
-            if (cost < best - 1e-9) {
+            if (even && cost < best - 1e-9) {
                 best = cost;
                 *split_out = (int)d;
                 *half_out = half != 0;
             }
+            if (!even && cost < best_uneven - 1e-9) {
+                best_uneven = cost;
+                uneven_split = (int)d;
+                uneven_half = half != 0;
+            }
         }
+    }
+    if (best_uneven < kUnevenGain * best) {
+        *split_out = uneven_split;
+        *half_out = uneven_half;
     }
 }
 
@@ -125,7 +149,8 @@ static bool block_ok(int64_t K, int64_t block)
     return block >= FP6_TILE && block % FP6_TILE == 0 && ((block / FP6_TILE) & (block / FP6_TILE - 1)) == 0 && K % block == 0;
 }
 
-bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int variant, int split_k, LinearPlan* plan)
+bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int variant, int split_k, LinearPlan* plan,
+               bool even_only)
 {
     const int64_t ktiles = K / FP6_TILE, nblocks = N / FP6_TILE;
     // tuning hints ride in the upper bits of `variant`; 0 = automatic
@@ -171,6 +196,7 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
     // four give twice the workgroups where there are few (measured: 40 against 47 us at 32 x 28672 x 8192, 24
     // against 30 us at 512 x 1024 x 8192, 20.7 against 30 us at 128 x 5120 x 5120).  The cost model below chooses.
     const bool plain = format == kE3M2 && !block && !hint_dequant;
+    even_only = even_only || split_k || variant_hints || !uneven_worth_a_look(plain, N, K);
     const bool narrow_ok = !hint_dequant && variant == FP6_VARIANT_GEMM;      // every format but the ablations
     int64_t gbn = hint_gbn ? hint_gbn : 8;
     p.gbn = (int)gbn;
@@ -188,7 +214,7 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
         if ((M <= 16 ? nblocks < 256 : true) && !hint_depth && waves_now == 4 && ktiles >= 8) {
             const bool may_half = half_ok && M <= 4 && hint_half != 2;
             plan_small_decode(M, nblocks, ktiles, format == kE3M1 ? 2560 : 3072, waves_now, split_k, may_half,
-                              hint_half == 1, &model_split, &model_half);
+                              hint_half == 1, even_only, &model_split, &model_half);
         }
         p.half_tiles = hint_half == 1 || (hint_half == 0 && model_half);
         if ((hint_waves && hint_waves != 4 && hint_waves != 8) || hint_bm || hint_meet > 2 ||
@@ -207,7 +233,7 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
                     : pick_decode_split(p.half_tiles ? 2 * nblocks : nblocks, ktiles, p.waves);
         if (block) {
             // the scales of a workgroup's K-slice are staged in LDS, 128 bytes per block of K: keep that under 96 KB
-            auto lds = [&](int64_t d) { return (((ktiles / d - 1) >> p.gshift) + 2) * 128; };
+            auto lds = [&](int64_t d) { return ((((ktiles + d - 1) / d - 1) >> p.gshift) + 2) * 128; };
             if (lds(p.split_k) > 96 * 1024) {
                 if (split_k) return false;
                 int64_t d = p.split_k;
@@ -230,7 +256,9 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
         // ceil(pairs per die x row blocks / (32 or 64)) rounds;
         // a round costs its k tiles at the per-tile time of the workgroup shape (or of the HBM stream, whichever
         // is longer) plus a fixed part that grows with the number of slices the last workgroup of a tile adds up.
-        double best_cost = 0.0;
+        double best_cost = 0.0, uneven_cost = 0.0;
+        int uneven_bm = 0, uneven_split = 0;
+        int64_t uneven_gbn = 0;
         if (block && hint_bm > 64) return false;        // fine-grained scales: two accumulators per tile
         int64_t best_gbn = gbn;
         for (int64_t g = 8; g >= 4; g -= 4) {
@@ -244,16 +272,27 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
                 const double slice = c.slice[bi] * (double)g / 8.0;
                 const int64_t cap = g == 4 ? 2 : 1;          // four-wavefront workgroups: two per compute unit
                 for (int64_t d = 1; d <= ktiles && d <= 64; d++) {
-                    if (ktiles % d || (split_k && d != split_k)) continue;
+                    const bool even = ktiles % d == 0;
+                    if ((!even && (even_only || 2 * d > ktiles)) || (split_k && d != split_k)) continue;
                     if (d > 1 && t > kMaxCounters) break;
                     const int64_t wgs = t * d, resident = wgs < 256 * cap ? wgs : 256 * cap;
                     const int64_t per_die = (nblk * d + 7) / 8 * mblk;
                     const int64_t rounds = (per_die + 32 * cap - 1) / (32 * cap);
+                    // uneven slices only with a compute unit to themselves: two four-wavefront workgroups that share one fall
+                    // further behind the model (bf16, 333 x 13824 x 5120 in three: 66.4 us, whole 59.2; 1325 x 4288 x 2368: 43.0, 33.1)
+                    if (!even && cap == 2 && per_die > 32) continue;
                     const double step = step1 * (cap == 2 && per_die > 32 ? c.shared_unit : 1.0);   // two sharing a unit
                     const double hbm_step = 3072.0 * (double)g * (double)resident / (double)mblk / c.hbm_tiled;
-                    const double cost = (double)rounds * ((double)(ktiles / d) * (step > hbm_step ? step : hbm_step) + c.round_fixed +
+                    const double cost = (double)rounds * ((double)((ktiles + d - 1) / d) * (step > hbm_step ? step : hbm_step) + c.round_fixed +
                                                           (d > 1 ? c.split_fixed + (double)d * slice : 0.0));
-                    if (best_cost == 0.0 || cost < best_cost) {
+                    if (!even) {
+                        if (uneven_cost == 0.0 || cost < uneven_cost) {
+                            uneven_cost = cost;
+                            uneven_bm = bm;
+                            uneven_split = (int)d;
+                            uneven_gbn = g;
+                        }
+                    } else if (best_cost == 0.0 || cost < best_cost) {
                         best_cost = cost;
                         p.block_m = bm;
                         p.split_k = (int)d;
@@ -263,6 +302,12 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
             }
         }
         if (best_cost == 0.0) return false;
+        if (uneven_cost > 0.0 && uneven_cost < kUnevenGain * best_cost) {
+            p.block_m = uneven_bm;
+            p.split_k = uneven_split;
+            best_gbn = uneven_gbn;
+        }
+        const bool even = ktiles % p.split_k == 0;
         gbn = best_gbn;
         p.gbn = (int)gbn;
         if (hint_kw) {
@@ -270,7 +315,7 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
             if (!plain || gbn != 4 || p.block_m != 128 || (ktiles / p.split_k) % 2) return false;
             p.kw = 2;
         } else if (plain && !variant_hints && !split_k && p.block_m == 128 && p.split_k > 1 &&
-                   ((M + 127) / 128) * ((nblocks + 3) / 4) <= kMaxCounters) {
+                   (even || ktiles % 2 == 0) && ((M + 127) / 128) * ((nblocks + 3) / 4) <= kMaxCounters) {
             // Where the model splits K, two of the K-ways can stay inside a workgroup of 128 x 256 (eight wavefronts
             // that add their sums in LDS): the same workgroups and the same work per compute unit, with half the partial
             // sums travelling through the workspace.  Measured at M = 512: 8192 x 22016 in four slices 170 -> 153 us,
@@ -283,7 +328,7 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
             } else if (gbn == 4 && wgs4 >= 512 && p.split_k % 2 == 0) {
                 p.split_k /= 2;
                 p.kw = 2;
-            } else if (gbn == 4 && wgs4 <= 256 && (ktiles / p.split_k) % 2 == 0) {
+            } else if (gbn == 4 && wgs4 <= 256 && (!even || (ktiles / p.split_k) % 2 == 0)) {
                 p.kw = 2;
             }
             p.gbn = (int)gbn;
@@ -412,7 +457,12 @@ static int linear_any(int format, const uint16_t* X, int64_t M, const void* hi_p
         return FP6_ERR_ALIGN;
     LinearPlan p;
     if (!make_plan(format, M, N, K, block, variant, split_k, &p)) return FP6_ERR_VARIANT;
-    const size_t need = plan_workspace(p);
+    size_t need = plan_workspace(p);
+    if (need > 0 && (!workspace || workspace_bytes < need)) {
+        // uneven slices may need more than even ones: a workspace that serves the latter is still enough
+        if (!make_plan(format, M, N, K, block, variant, split_k, &p, true)) return FP6_ERR_VARIANT;
+        need = plan_workspace(p);
+    }
     if (need > 0 && (!workspace || workspace_bytes < need)) return FP6_ERR_WORKSPACE;
     forget_earlier_errors();
     hipError_t e = (p.variant == FP6_VARIANT_DECODE)
@@ -423,7 +473,7 @@ static int linear_any(int format, const uint16_t* X, int64_t M, const void* hi_p
 
 // A group of layers can share one launch if the streaming kernel serves them (M <= 16) and they have one K:
 // their channel blocks are then planned as the blocks of one layer with the summed N.
-static bool group_shares_a_launch(int64_t M, const fp6_linear_problem* pr, int count, LinearPlan* plan)
+static bool group_shares_a_launch(int64_t M, const fp6_linear_problem* pr, int count, LinearPlan* plan, bool even_only = false)
 {
     if (count < 2 || M > 16) return false;
     int64_t n_total = 0;
@@ -432,7 +482,7 @@ static bool group_shares_a_launch(int64_t M, const fp6_linear_problem* pr, int c
         n_total += pr[i].N;
     }
     if (!shape_ok(n_total, pr[0].K)) return false;
-    if (!make_plan(kE3M2, M, n_total, pr[0].K, 0, FP6_VARIANT_AUTO, 0, plan)) return false;
+    if (!make_plan(kE3M2, M, n_total, pr[0].K, 0, FP6_VARIANT_AUTO, 0, plan, even_only)) return false;
     return plan->variant == FP6_VARIANT_DECODE && plan->block_m == 16 && plan->waves == 4 && plan->depth == 4;
 }
 
@@ -549,10 +599,19 @@ int fp6_linear_group(int64_t M, const fp6_linear_problem* problems, int count, v
     const int bad = group_check(M, problems, count);
     if (bad != FP6_OK) return bad;
     if (!aligned16(workspace)) return FP6_ERR_ALIGN;
-    const size_t need = fp6_linear_group_workspace_bytes(M, problems, count);
-    if (need > 0 && (!workspace || workspace_bytes < need)) return FP6_ERR_WORKSPACE;
     LinearPlan p;
-    if (group_shares_a_launch(M, problems, count, &p)) {
+    bool shared = group_shares_a_launch(M, problems, count, &p);
+    if (shared && plan_workspace(p) > (workspace ? workspace_bytes : 0)) shared = group_shares_a_launch(M, problems, count, &p, true);
+    if (shared && plan_workspace(p) > (workspace ? workspace_bytes : 0)) return FP6_ERR_WORKSPACE;
+    if (!shared) {
+        // every layer's need is checked before the first of them is launched
+        for (int i = 0; i < count; i++) {
+            LinearPlan q;
+            if (!make_plan(kE3M2, M, problems[i].N, problems[i].K, 0, FP6_VARIANT_AUTO, 0, &q, true)) continue;
+            if (plan_workspace(q) > (workspace ? workspace_bytes : 0)) return FP6_ERR_WORKSPACE;
+        }
+    }
+    if (shared) {
         GroupLayer layers[FP6_GROUP_MAX];
         for (int i = 0; i < count; i++)
             layers[i] = GroupLayer{problems[i].X, problems[i].hi_plane, problems[i].lo_plane, problems[i].scales, problems[i].Y,
@@ -625,7 +684,11 @@ int fp6_linear_static(const uint16_t* X, int64_t M, const void* hi_plane, const 
         return FP6_ERR_ALIGN;
     LinearPlan p;
     if (!make_plan(kE3M2, M, N, K, 0, FP6_VARIANT_AUTO, 0, &p)) return FP6_ERR_VARIANT;
-    const size_t need = plan_workspace(p);
+    size_t need = plan_workspace(p);
+    if (need > (size_t)FP6_STATIC_SCRATCH_BYTES) {
+        if (!make_plan(kE3M2, M, N, K, 0, FP6_VARIANT_AUTO, 0, &p, true)) return FP6_ERR_VARIANT;
+        need = plan_workspace(p);
+    }
     if (need > (size_t)FP6_STATIC_SCRATCH_BYTES) return FP6_ERR_SCRATCH;
     void* ws = nullptr;
     if (need > 0) {

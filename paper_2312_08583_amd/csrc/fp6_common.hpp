@@ -26,6 +26,14 @@ constexpr int kLo1TileBytes = 512;    // 1-bit plane bytes per tile (FP5): 8 byt
 template <int FMT>
 constexpr int kLoBytesOf = FMT == kE3M1 ? kLo1TileBytes : kLoTileBytes;
 
+// First of the `units` equal pieces of K (k tiles, or pairs of them) that K-slice s works on: the slices are as even as
+// whole pieces allow, the first units % split_k of them one piece longer.  s = split_k gives the end.
+__device__ __forceinline__ int slice_begin(int units, int split_k, int s)
+{
+    const int per = units / split_k, longer = units - per * split_k;
+    return s * per + min(s, longer);
+}
+
 // bitwise select: mask bit 1 -> a, mask bit 0 -> b   (one v_bitop3_b32)
 __device__ __forceinline__ uint32_t bit_select(uint32_t a, uint32_t b, uint32_t mask)
 {

@@ -82,8 +82,7 @@ __device__ __forceinline__ void decode_block(
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int ktiles = K / kTile;
-    const int kt_per = ktiles / split_k;
-    const int kt_end = (s + 1) * kt_per;
+    const int kt_begin = slice_begin(ktiles, split_k, s), kt_end = slice_begin(ktiles, split_k, s + 1);
     static_assert(MB == 1 || !FGQ, "several row blocks: row-wise scales only");
     const int m = lane & 15, g = lane >> 4;
     const uint16_t* xrow[MB];
@@ -104,7 +103,7 @@ __device__ __forceinline__ void decode_block(
     // FGQ: this workgroup's scales -> LDS (16-byte pieces; piece c = block group0 + c/8, channels 8*(c%8)..+7),
     // four loads per thread in flight
     extern __shared__ __align__(16) uint16_t gscale[];
-    const int group0 = (s * kt_per) >> gshift;
+    const int group0 = kt_begin >> gshift;
     if (FGQ) {
         constexpr int T = WAVES * 64;
         const int pieces = (((kt_end - 1) >> gshift) - group0 + 1) * 8;
@@ -123,7 +122,7 @@ __device__ __forceinline__ void decode_block(
     }
 
     // this wavefront's tiles: kt0, kt0 + WAVES, ...  (cnt of them, possibly none)
-    const int kt0 = s * kt_per + wave;
+    const int kt0 = kt_begin + wave;
     const int cnt = (kt_end - kt0 + WAVES - 1) / WAVES;
     if (cnt > 0) {
         TileRaw raw[D];
@@ -366,8 +365,7 @@ __device__ __forceinline__ void decode_half_block(
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int ktiles = K / kTile;
-    const int kt_per = ktiles / split_k;
-    const int kt_end = (s + 1) * kt_per;
+    const int kt_begin = slice_begin(ktiles, split_k, s), kt_end = slice_begin(ktiles, split_k, s + 1);
     const int m = lane & 15, g = lane >> 4;
     const uint16_t* xrow = X + (size_t)min(m, M - 1) * K + g * 8;
     const size_t tile0 = (size_t)nb * ktiles;
@@ -387,7 +385,7 @@ __device__ __forceinline__ void decode_half_block(
         }
     };
 
-    const int kt0 = s * kt_per + wave;
+    const int kt0 = kt_begin + wave;
     const int cnt = (kt_end - kt0 + WAVES - 1) / WAVES;
     if (cnt > 0) {
         HalfRaw raw[D];
@@ -537,7 +535,7 @@ static hipError_t launch_decode_t(const LinearPlan& p, const uint16_t* X, int64_
     unsigned long long* slots = reinterpret_cast<unsigned long long*>(reinterpret_cast<char*>(workspace) + kCounterBytes);
     const unsigned grid = (unsigned)((N / kTile) * p.split_k);
     // FGQ: 128 bytes of scales per block of K in a workgroup's slice (a slice may start inside a block)
-    const size_t lds = FGQ ? (size_t)(((K / kTile / p.split_k - 1) >> p.gshift) + 2) * 128 : 0;
+    const size_t lds = FGQ ? (size_t)((((K / kTile + p.split_k - 1) / p.split_k - 1) >> p.gshift) + 2) * 128 : 0;
     hipLaunchKernelGGL((decode_kernel<WAVES, D, DQ, FGQ, FMT, MB>), dim3(grid), dim3(WAVES * 64), lds, stream, X, (int)M,
                        (const u32x4*)hi, (const u32x4*)lo, scales, (int)N, (int)K, Y, partials, counters, slots,
                        p.split_k, p.pairwise, p.gshift);

@@ -144,8 +144,7 @@ __global__ __launch_bounds__(GBN / WN * KW * 64, (GBN == 4 && KW == 1) ? 2 : 1) 
     const int pair = id * 8 + xcd;
     if (pair >= nblk * split_k) return;      // the grid is padded to a multiple of eight pairs
     const int nbw = pair / split_k, s = pair % split_k;
-    const int kt_per = ktiles / split_k;
-    const int kt_begin = s * kt_per, kt_end = kt_begin + kt_per;
+    const int kt_begin = slice_begin(ktiles / KW, split_k, s) * KW, kt_end = slice_begin(ktiles / KW, split_k, s + 1) * KW;
     const int m0 = mb * BM;
     const int nb0 = nbw * GBN + nw * WN;       // first block of output channels of this wavefront
     const int i = lane & 15, g = lane >> 4;

@@ -55,8 +55,9 @@ struct LinearPlan {
 };
 
 // Heuristic (or caller-forced) plan; returns false if the request is invalid for the shape.
-// `block` = elements along K per scale (0 = row-wise).
-bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int variant, int split_k, LinearPlan* plan);
+// `block` = elements along K per scale (0 = row-wise).  even_only: no K-slices of different lengths.
+bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int variant, int split_k, LinearPlan* plan,
+               bool even_only = false);
 
 // One layer of a group of layers launched together (fp6_linear_group).
 struct GroupLayer {

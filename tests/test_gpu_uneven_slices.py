@@ -1,0 +1,67 @@
+"""K-slices of different lengths: K/64 that the planner's split does not divide, in both kernel families and every format.
+On the GPU against the oracle, with the planner's workspace and with one that only the even split fits."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2312_08583_amd as P
+from oracle import fp6_oracle as O
+from paper_2312_08583_amd import binding as B
+from paper_2312_08583_amd import inputs
+
+from gpu_util import assert_y_close, to_np16
+
+DEV = "cuda"
+FORMATS = {"fp6": 6, "fp5": 5, "v2": 7, "bf16": 8, "fgq": 6}
+# (format, M, N, K); the last five: streaming kernel
+SHAPES = [("fp6", 79, 2752, 9344), ("fp6", 130, 1152, 73 * 64), ("fp6", 333, 1024, 202 * 64), ("fp5", 70, 1152, 67 * 64),
+          ("v2", 200, 1152, 79 * 64), ("bf16", 333, 1152, 94 * 64), ("fgq", 66, 1152, 106 * 64),
+          ("fp6", 1, 1088, 101 * 64), ("fp6", 16, 1088, 131 * 64), ("fp6", 40, 1088, 131 * 64), ("fp5", 3, 1088, 101 * 64),
+          ("fgq", 5, 1088, 202 * 64)]
+
+
+def _plan(fmt, M, N, K, **kw):
+    return P.fp6_linear_plan(M, N, K, format=FORMATS[fmt], block=128 if fmt == "fgq" else 0, **kw)
+
+
+@pytest.mark.parametrize("fmt,M,N,K", SHAPES)
+def test_the_planner_splits_these_unevenly(fmt, M, N, K):
+    plan = _plan(fmt, M, N, K)
+    assert (K // 64) % plan["split_k"] != 0, P.plan_text(plan)
+    with pytest.raises(P.Fp6Error):               # a forced split still has to divide K/64
+        _plan(fmt, M, N, K, split_k=plan["split_k"])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fmt,M,N,K", SHAPES)
+def test_uneven_slices(fmt, M, N, K):
+    block = 128
+    W = inputs.weight(N, K, seed=7100 + M, sigma=0.02, outlier_frac=0.001, device=DEV)
+    X = (inputs.activation_bf16 if fmt == "bf16" else inputs.activation)(M, K, seed=7200 + M, device=DEV)
+    xb, wb = X.cpu().view(torch.int16).numpy().view(np.uint16), to_np16(W)
+    if fmt == "fgq":
+        codes, scales = O.quantize_fgq(wb, block)
+        planes, Yref = P.fp6_quantize_pack_fgq(W, block), O.linear_fgq(xb, codes, scales, block)
+        call = lambda ws: P.fp6_linear_fgq(X, *planes, N, K, block, workspace=ws)
+    else:
+        codes, scales = (O.quantize5 if fmt == "fp5" else O.quantize)(wb)
+        planes = {"fp6": P.fp6_quantize_pack, "fp5": P.fp5_quantize_pack}.get(fmt, P.fp6_quantize_pack_v2)(W)
+        Yref = {"fp5": O.linear5, "bf16": O.linear_bf16}.get(fmt, O.linear)(xb, codes, scales)
+        fn = {"fp6": P.fp6_linear, "fp5": P.fp5_linear, "v2": P.fp6_linear_v2, "bf16": P.fp6_linear_v2_bf16}[fmt]
+        call = lambda ws: fn(X, *planes, N, K, workspace=ws)
+    need = _plan(fmt, M, N, K)["workspace_bytes"]
+    ws, short = P.new_workspace(need, DEV), P.new_workspace(need - 16, DEV)
+    Y = [call(ws), call(ws)]
+    assert not ws[:B.FP6_WORKSPACE_ZERO_BYTES].any()
+    try:
+        Y.append(call(short))                     # the even split, where it needs less
+    except P.Fp6Error:
+        pass
+    torch.cuda.synchronize()
+    assert torch.equal(Y[0], Y[1])
+    for y in Y:
+        if fmt == "bf16":
+            yd = y.cpu().double().numpy()         # half a unit in the last of 8 significant bits, and the fp32 sums
+            assert (np.abs(yd - Yref) <= 2.0 ** -8 * np.abs(Yref) + 1e-4 * (np.abs(Yref) + np.sqrt(np.mean(Yref ** 2)))).all()
+        else:
+            assert_y_close(y, Yref, (fmt, M, N, K))
