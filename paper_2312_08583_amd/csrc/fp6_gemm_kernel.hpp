@@ -20,12 +20,13 @@
 // The DMA is issued from inline assembly and waited for with explicit s_waitcnt vmcnt:
 // every step issues the same number of loads per wavefront, so "at most (D-2) groups
 // still in flight" is a constant, and the compiler (which cannot see these loads) has
-// no reason to drain the queue.  One barrier per k tile publishes the landed stage and
-// frees the stage consumed in the previous step.
+// no reason to drain the queue.  One barrier per k tile publishes the next step's stage and
+// frees this step's, whose operands are in registers by then (see step()).
 //
 // LDS traffic per k tile: every wavefront reads the whole X slice (wavefronts x BM x 128 B) plus its
 // planes - at BM = 128 about 152 KB per 2048 MFMA cycles of a SIMD, some 60 % of the 128 B/clk port.
-// Measured, the loop keeps the matrix pipe busy 40-50 % of the time at BM = 128 and less at smaller BM,
+// Measured (before a step's operands were read ahead of its barrier, which gave 1-2 % at 128 rows in fp16, 13 % in bf16,
+// 5-9 % on row counts between 64 and 1300), the loop keeps the matrix pipe busy 40-50 % of the time at BM = 128 and less at smaller BM,
 // where a k tile holds too few MFMAs per barrier.  With the loads, the barrier, the unpack or the X
 // reads taken out one at a time the loop gets no more than 10 % faster, and with all of them out 18 %:
 // no single stage is the limit.  The shader clock under this kernel stays at 2.1-2.4 GHz of 2.4 on
@@ -39,10 +40,6 @@
 #include "fp6_common.hpp"
 #include "fp6_internal.hpp"
 #include "fp6_reduce.hpp"
-
-#ifndef FP6_GEMM_HINTS
-#define FP6_GEMM_HINTS 1
-#endif
 
 namespace fp6 {
 
@@ -265,24 +262,10 @@ __global__ __launch_bounds__(GBN / WN * KW * 64, (GBN == 4 && KW == 1) ? 2 : 1) 
         }
     };
 
-    // Issue order.  Bias-shift FP6 at up to 64 rows: after the first fragment every MFMA (16 cycles in the matrix pipe) is
-    // followed by a few of the unpack VALU operations and, while there are any, one of the LDS reads, in its shadow.
-    // Plane layout 2 at 128 rows: an LDS read behind each of the first MFMAs (333 x 13824 x 5120 in bf16: 59.0 us, 63.0
-    // without).  The rest is left to the compiler: at 128 rows the first pattern spills, and the second costs bias-shift
-    // FP6 5 % (512 x 22016 x 8192: 170.0 us, 162.9 without).
+    // Issue order, plane layout 2 at 128 rows: an LDS read behind each of the first MFMAs (333 x 13824 x 5120 in bf16:
+    // 59.0 us, 63.0 without).  The rest is left to the compiler: that pattern costs bias-shift FP6 5 % (512 x 22016 x 8192:
+    // 170.0 us, 162.9 without), and VALU operations grouped behind every MFMA spill at 128 rows and lose 1-2 % below.
     auto hints = [&](int part_of_step) {
-#if FP6_GEMM_HINTS
-        if (kWhole && !FGQ && FMT == kE3M2 && DQ != kHalfMul) {
-            const int reads = part_of_step == 1 ? MT : 3 * WN + (kWhole ? 2 * MT : MT);
-            const int mfmas = NT * MT * (kWhole ? 2 : 1);
-            __builtin_amdgcn_sched_group_barrier(0x002, 15, 0);
-#pragma unroll
-            for (int n = 0; n < mfmas; n++) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                if (n < reads) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
-            }
-        }
         if (!kWhole && layout2(FMT)) {
             const int reads = part_of_step == 1 ? MT : 3 * WN + MT;
 #pragma unroll
@@ -291,7 +274,6 @@ __global__ __launch_bounds__(GBN / WN * KW * 64, (GBN == 4 && KW == 1) ? 2 : 1) 
                 __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
             }
         }
-#endif
     };
 
     TileRaw raw[WN];                  // planes of the current step
