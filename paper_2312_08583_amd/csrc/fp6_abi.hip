@@ -370,6 +370,33 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
 
 static size_t plan_workspace(const LinearPlan& p) { return p.split_k > 1 ? kZeroBytes + p.partial_bytes : 0; }
 
+// What a call with `available` bytes of workspace runs: the plan that the workspace query reports on or, where that does
+// not fit, the one with even slices (which may need less).  `plan` holds the former; too little for both is an error.
+static int fit_workspace(int format, int64_t M, int64_t N, int64_t K, int64_t block, int variant, int split_k, size_t available,
+                         LinearPlan* plan)
+{
+    if (plan_workspace(*plan) <= available) return FP6_OK;
+    if (!make_plan(format, M, N, K, block, variant, split_k, plan, true)) return FP6_ERR_VARIANT;
+    return plan_workspace(*plan) <= available ? FP6_OK : FP6_ERR_WORKSPACE;
+}
+
+static int plan_within(int format, int64_t M, int64_t N, int64_t K, int64_t block, int variant, int split_k, size_t available,
+                       LinearPlan* plan)
+{
+    if (!make_plan(format, M, N, K, block, variant, split_k, plan)) return FP6_ERR_VARIANT;
+    return fit_workspace(format, M, N, K, block, variant, split_k, available, plan);
+}
+
+static int launch_plan(const LinearPlan& p, const uint16_t* X, int64_t M, const void* hi, const void* lo, const uint16_t* scales,
+                       int64_t N, int64_t K, uint16_t* Y, void* workspace, void* stream)
+{
+    forget_earlier_errors();
+    const hipError_t e = (p.variant == FP6_VARIANT_DECODE)
+                             ? launch_decode(p, X, M, hi, lo, scales, N, K, Y, workspace, (hipStream_t)stream)
+                             : launch_gemm(p, X, M, hi, lo, scales, N, K, Y, workspace, (hipStream_t)stream);
+    return e == hipSuccess ? FP6_OK : FP6_ERR_HIP;
+}
+
 }  // namespace fp6
 
 using namespace fp6;
@@ -456,24 +483,13 @@ static int linear_any(int format, const uint16_t* X, int64_t M, const void* hi_p
         !aligned16(workspace))
         return FP6_ERR_ALIGN;
     LinearPlan p;
-    if (!make_plan(format, M, N, K, block, variant, split_k, &p)) return FP6_ERR_VARIANT;
-    size_t need = plan_workspace(p);
-    if (need > 0 && (!workspace || workspace_bytes < need)) {
-        // uneven slices may need more than even ones: a workspace that serves the latter is still enough
-        if (!make_plan(format, M, N, K, block, variant, split_k, &p, true)) return FP6_ERR_VARIANT;
-        need = plan_workspace(p);
-    }
-    if (need > 0 && (!workspace || workspace_bytes < need)) return FP6_ERR_WORKSPACE;
-    forget_earlier_errors();
-    hipError_t e = (p.variant == FP6_VARIANT_DECODE)
-                       ? launch_decode(p, X, M, hi_plane, lo_plane, scales, N, K, Y, workspace, (hipStream_t)stream)
-                       : launch_gemm(p, X, M, hi_plane, lo_plane, scales, N, K, Y, workspace, (hipStream_t)stream);
-    return e == hipSuccess ? FP6_OK : FP6_ERR_HIP;
+    const int rc = plan_within(format, M, N, K, block, variant, split_k, workspace ? workspace_bytes : 0, &p);
+    return rc == FP6_OK ? launch_plan(p, X, M, hi_plane, lo_plane, scales, N, K, Y, workspace, stream) : rc;
 }
 
 // A group of layers can share one launch if the streaming kernel serves them (M <= 16) and they have one K:
 // their channel blocks are then planned as the blocks of one layer with the summed N.
-static bool group_shares_a_launch(int64_t M, const fp6_linear_problem* pr, int count, LinearPlan* plan, bool even_only = false)
+static bool group_shares_a_launch(int64_t M, const fp6_linear_problem* pr, int count, int64_t* n_sum, LinearPlan* plan)
 {
     if (count < 2 || M > 16) return false;
     int64_t n_total = 0;
@@ -481,8 +497,9 @@ static bool group_shares_a_launch(int64_t M, const fp6_linear_problem* pr, int c
         if (pr[i].K != pr[0].K) return false;
         n_total += pr[i].N;
     }
+    *n_sum = n_total;
     if (!shape_ok(n_total, pr[0].K)) return false;
-    if (!make_plan(kE3M2, M, n_total, pr[0].K, 0, FP6_VARIANT_AUTO, 0, plan, even_only)) return false;
+    if (!make_plan(kE3M2, M, n_total, pr[0].K, 0, FP6_VARIANT_AUTO, 0, plan)) return false;
     return plan->variant == FP6_VARIANT_DECODE && plan->block_m == 16 && plan->waves == 4 && plan->depth == 4;
 }
 
@@ -584,7 +601,8 @@ size_t fp6_linear_group_workspace_bytes(int64_t M, const fp6_linear_problem* pro
 {
     if (group_check(M, problems, count) != FP6_OK) return 0;
     LinearPlan p;
-    if (group_shares_a_launch(M, problems, count, &p)) return plan_workspace(p);
+    int64_t n_total;
+    if (group_shares_a_launch(M, problems, count, &n_total, &p)) return plan_workspace(p);
     size_t need = 0;
     for (int i = 0; i < count; i++) {
         const size_t n = workspace_any(kE3M2, M, problems[i].N, problems[i].K, 0, FP6_VARIANT_AUTO, 0);
@@ -599,32 +617,30 @@ int fp6_linear_group(int64_t M, const fp6_linear_problem* problems, int count, v
     const int bad = group_check(M, problems, count);
     if (bad != FP6_OK) return bad;
     if (!aligned16(workspace)) return FP6_ERR_ALIGN;
-    LinearPlan p;
-    bool shared = group_shares_a_launch(M, problems, count, &p);
-    if (shared && plan_workspace(p) > (workspace ? workspace_bytes : 0)) shared = group_shares_a_launch(M, problems, count, &p, true);
-    if (shared && plan_workspace(p) > (workspace ? workspace_bytes : 0)) return FP6_ERR_WORKSPACE;
-    if (!shared) {
-        // every layer's need is checked before the first of them is launched
-        for (int i = 0; i < count; i++) {
-            LinearPlan q;
-            if (!make_plan(kE3M2, M, problems[i].N, problems[i].K, 0, FP6_VARIANT_AUTO, 0, &q, true)) continue;
-            if (plan_workspace(q) > (workspace ? workspace_bytes : 0)) return FP6_ERR_WORKSPACE;
-        }
-    }
-    if (shared) {
+    const size_t available = workspace ? workspace_bytes : 0;
+    LinearPlan plans[FP6_GROUP_MAX];
+    int64_t n_total;
+    if (group_shares_a_launch(M, problems, count, &n_total, &plans[0])) {
+        const int rc = fit_workspace(kE3M2, M, n_total, problems[0].K, 0, FP6_VARIANT_AUTO, 0, available, &plans[0]);
+        if (rc != FP6_OK) return rc;
         GroupLayer layers[FP6_GROUP_MAX];
         for (int i = 0; i < count; i++)
             layers[i] = GroupLayer{problems[i].X, problems[i].hi_plane, problems[i].lo_plane, problems[i].scales, problems[i].Y,
                                    problems[i].N};
         forget_earlier_errors();
-        return launch_decode_group(p, count, layers, M, problems[0].K, workspace, (hipStream_t)stream) == hipSuccess ? FP6_OK
-                                                                                                                    : FP6_ERR_HIP;
+        return launch_decode_group(plans[0], count, layers, M, problems[0].K, workspace, (hipStream_t)stream) == hipSuccess
+                   ? FP6_OK
+                   : FP6_ERR_HIP;
     }
-    // one layer after another on the stream; they share the workspace in turn
+    // one layer after another on the stream; they share the workspace in turn.  Every layer is planned before the first
+    // of them is launched.
     for (int i = 0; i < count; i++) {
-        const int rc = linear_any(kE3M2, problems[i].X, M, problems[i].hi_plane, problems[i].lo_plane, problems[i].scales,
-                                  problems[i].N, problems[i].K, 0, problems[i].Y, workspace, workspace_bytes, stream,
-                                  FP6_VARIANT_AUTO, 0);
+        const int rc = plan_within(kE3M2, M, problems[i].N, problems[i].K, 0, FP6_VARIANT_AUTO, 0, available, &plans[i]);
+        if (rc != FP6_OK) return rc;
+    }
+    for (int i = 0; i < count; i++) {
+        const int rc = launch_plan(plans[i], problems[i].X, M, problems[i].hi_plane, problems[i].lo_plane, problems[i].scales,
+                                   problems[i].N, problems[i].K, problems[i].Y, workspace, stream);
         if (rc != FP6_OK) return rc;
     }
     return FP6_OK;
@@ -683,23 +699,14 @@ int fp6_linear_static(const uint16_t* X, int64_t M, const void* hi_plane, const 
     if (!aligned16(X) || !aligned16(hi_plane) || !aligned16(lo_plane) || !aligned16(scales) || !aligned16(Y))
         return FP6_ERR_ALIGN;
     LinearPlan p;
-    if (!make_plan(kE3M2, M, N, K, 0, FP6_VARIANT_AUTO, 0, &p)) return FP6_ERR_VARIANT;
-    size_t need = plan_workspace(p);
-    if (need > (size_t)FP6_STATIC_SCRATCH_BYTES) {
-        if (!make_plan(kE3M2, M, N, K, 0, FP6_VARIANT_AUTO, 0, &p, true)) return FP6_ERR_VARIANT;
-        need = plan_workspace(p);
-    }
-    if (need > (size_t)FP6_STATIC_SCRATCH_BYTES) return FP6_ERR_SCRATCH;
+    const int rc = plan_within(kE3M2, M, N, K, 0, FP6_VARIANT_AUTO, 0, FP6_STATIC_SCRATCH_BYTES, &p);
+    if (rc != FP6_OK) return rc == FP6_ERR_WORKSPACE ? FP6_ERR_SCRATCH : rc;
     void* ws = nullptr;
-    if (need > 0) {
+    if (plan_workspace(p) > 0) {
         ws = static_scratch((hipStream_t)stream);
         if (!ws) return FP6_ERR_HIP;
     }
-    forget_earlier_errors();
-    hipError_t e = (p.variant == FP6_VARIANT_DECODE)
-                       ? launch_decode(p, X, M, hi_plane, lo_plane, scales, N, K, Y, ws, (hipStream_t)stream)
-                       : launch_gemm(p, X, M, hi_plane, lo_plane, scales, N, K, Y, ws, (hipStream_t)stream);
-    return e == hipSuccess ? FP6_OK : FP6_ERR_HIP;
+    return launch_plan(p, X, M, hi_plane, lo_plane, scales, N, K, Y, ws, stream);
 }
 
 int fp6_linear_fgq(const uint16_t* X, int64_t M, const void* hi_plane, const void* lo_plane, const uint16_t* scales,

@@ -1,5 +1,6 @@
 """K-slices of different lengths: K/64 that the planner's split does not divide, in both kernel families and every format.
-On the GPU against the oracle, with the planner's workspace and with one that only the even split fits."""
+On the GPU against the oracle, with the planner's workspace and with one that only the even split fits; in groups and on
+the static scratch."""
 import numpy as np
 import pytest
 import torch
@@ -9,7 +10,7 @@ from oracle import fp6_oracle as O
 from paper_2312_08583_amd import binding as B
 from paper_2312_08583_amd import inputs
 
-from gpu_util import assert_y_close, to_np16
+from gpu_util import assert_y_close, oracle_reference, to_np16
 
 DEV = "cuda"
 FORMATS = {"fp6": 6, "fp5": 5, "v2": 7, "bf16": 8, "fgq": 6}
@@ -65,3 +66,49 @@ def test_uneven_slices(fmt, M, N, K):
             assert (np.abs(yd - Yref) <= 2.0 ** -8 * np.abs(Yref) + 1e-4 * (np.abs(Yref) + np.sqrt(np.mean(Yref ** 2)))).all()
         else:
             assert_y_close(y, Yref, (fmt, M, N, K))
+
+
+def _fp6_layers(M, shapes, seed):
+    made = []
+    for i, (N, K) in enumerate(shapes):
+        W = inputs.weight(N, K, seed=seed + i, sigma=0.02, outlier_frac=0.001, device=DEV)
+        X = inputs.activation(M, K, seed=seed + 50 + i, device=DEV)
+        made.append(((X,) + tuple(P.fp6_quantize_pack(W)) + (N, K), oracle_reference(W, X)[2]))
+    return [layer for layer, _ in made], [Yref for _, Yref in made]
+
+
+# groups: one launch over the summed N; in sequence at more than 16 rows (even slices need more workspace than the
+# uneven ones there); in sequence with different K
+GROUPS = [(2, [(576, 101 * 64), (512, 101 * 64)]), (17, [(1024, 10816), (1024, 10816)]), (2, [(1088, 101 * 64), (1088, 131 * 64)])]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,shapes", GROUPS)
+def test_groups_of_uneven_layers(M, shapes):
+    shared = M <= 16 and len({K for _, K in shapes}) == 1
+    for N, K in [(sum(N for N, _ in shapes), shapes[0][1])] if shared else shapes:
+        assert (K // 64) % P.fp6_linear_plan(M, N, K)["split_k"] != 0
+    layers, Yrefs = _fp6_layers(M, shapes, seed=7300 + M)
+    need = P.fp6_linear_group_workspace_bytes(M, shapes)
+    ws = P.new_workspace(need, DEV)
+    for _ in range(2):
+        ys = P.fp6_linear_group(layers, workspace=ws)
+        for Y, Yref in zip(ys, Yrefs):
+            assert_y_close(Y, Yref, (M, shapes))
+        assert not ws[:B.FP6_WORKSPACE_ZERO_BYTES].any()
+    for Y, Z in zip(ys, P.fp6_linear_group(layers)):           # the wrapper allocates what the query reports
+        assert torch.equal(Y, Z)
+    if not shared:
+        for layer, Y in zip(layers, ys):
+            assert torch.equal(Y, P.fp6_linear(*layer))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", [(17, 1024, 10816), (2, 1088, 101 * 64)])
+def test_uneven_slices_on_the_static_scratch(M, N, K):
+    assert (K // 64) % P.fp6_linear_plan(M, N, K)["split_k"] != 0
+    (layer,), (Yref,) = _fp6_layers(M, [(N, K)], seed=7400 + M)
+    for _ in range(2):
+        Y = P.fp6_linear_static(*layer)
+        assert_y_close(Y, Yref, (M, N, K))
+    assert torch.equal(Y, P.fp6_linear(*layer))
