@@ -106,20 +106,21 @@ static void plan_small_decode(int64_t M, int64_t nblocks, int64_t ktiles, int ti
     *split_out = forced_split ? forced_split : 1;
     *half_out = must_half;
     const double bytes = (double)nblocks * (double)ktiles * tile_bytes;
+    const PlanModel& c = kModel;
+    const bool rows16 = M <= 16;
+    const double stream = bytes / (rows16 ? c.stream16 : c.stream64);
+    const double slower = rows16 ? 1.0 : pow(16.0 / (double)M, c.wg_rows_exponent);
     for (int half = must_half ? 1 : 0; half <= (may_half || must_half ? 1 : 0); half++) {
+        // (FP5 half tiles fetch the 1-bit plane four bytes a lane: their lower rate separates 8192 x 8192, where they win, from 8192 x 22016, where they lose)
+        const double rate = rows16 ? (half ? (tile_bytes == 3072 ? c.wg_half : c.wg_half_fp5) : c.wg_full) : c.wg_full * slower;
         for (int64_t d = forced_split ? forced_split : 1; d <= (forced_split ? forced_split : 32) && d <= ktiles; d++) {
-            const bool even = ktiles % d == 0;
+            const uint32_t whole = (uint32_t)ktiles / (uint32_t)d;          // (ktiles <= 2^24)
+            const bool even = whole * (uint32_t)d == (uint32_t)ktiles;
             if (!even && even_only) continue;
-            if (d > 1 && ktiles / d < 2 * waves) break;       // every wavefront keeps at least two tiles
+            if (d > 1 && (int)whole < 2 * waves) break;       // every wavefront keeps at least two tiles
             const int64_t wgs = nblocks * d * (half ? 2 : 1);
             const double rounds = (double)((wgs + 255) / 256);
-            const bool rows16 = M <= 16;
-            const PlanModel& c = kModel;
-            const double stream = bytes / (rows16 ? c.stream16 : c.stream64);
-            // (FP5 half tiles fetch the 1-bit plane four bytes a lane: their lower rate separates 8192 x 8192, where they win, from 8192 x 22016, where they lose)
-            const double rate = rows16 ? (half ? (tile_bytes == 3072 ? c.wg_half : c.wg_half_fp5) : c.wg_full)
-                                       : c.wg_full * pow(16.0 / (double)M, c.wg_rows_exponent);
-            const double longest = (double)((ktiles + d - 1) / d * d) / (double)ktiles;     // the longest slice over the mean
+            const double longest = even ? 1.0 : (double)((int64_t)(whole + 1) * d) / (double)ktiles;     // the longest slice over the mean
             const double unit = rounds * (bytes / (double)wgs) * longest / rate;
             const double meet = d == 1 ? 0.0
                                 : rows16 ? (d == 2 ? c.meet_pair : c.meet_base16 + c.meet_slice16 * (double)d)
@@ -261,6 +262,17 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
         int64_t uneven_gbn = 0;
         if (block && hint_bm > 64) return false;        // fine-grained scales: two accumulators per tile
         int64_t best_gbn = gbn;
+        // the numbers of slices to look at, even and uneven ones, and the k tiles of their longest slice (ktiles <= 2^24)
+        const int most = ktiles < 64 ? (int)ktiles : 64;
+        int evens = 0, unevens = 0, even_d[64], uneven_d[64], slice_tiles[65];
+        for (int d = 1; d <= most; d++) {
+            const uint32_t whole = (uint32_t)ktiles / (uint32_t)d;
+            const bool even = whole * (uint32_t)d == (uint32_t)ktiles;
+            if ((!even && (even_only || 2 * d > ktiles)) || (split_k && d != split_k)) continue;
+            slice_tiles[d] = (int)whole + (even ? 0 : 1);
+            if (even) even_d[evens++] = d;
+            else uneven_d[unevens++] = d;
+        }
         for (int64_t g = 8; g >= 4; g -= 4) {
             if (hint_gbn ? g != hint_gbn : (g == 4 && !narrow_ok)) continue;
             for (int bm = 32; bm <= (block ? 64 : 128); bm *= 2) {
@@ -271,32 +283,36 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
                 const double step1 = c.step[bi] * (g == 8 ? 1.0 : c.narrow_step);
                 const double slice = c.slice[bi] * (double)g / 8.0;
                 const int64_t cap = g == 4 ? 2 : 1;          // four-wavefront workgroups: two per compute unit
-                for (int64_t d = 1; d <= ktiles && d <= 64; d++) {
-                    const bool even = ktiles % d == 0;
-                    if ((!even && (even_only || 2 * d > ktiles)) || (split_k && d != split_k)) continue;
-                    if (d > 1 && t > kMaxCounters) break;
+                const double hbm_unit = 3072.0 * (double)g / (double)mblk / c.hbm_tiled;
+                auto pairs_per_die = [&](int d) { return ((nblk * d + 7) >> 3) * mblk; };
+                auto cost_of = [&](int d, int64_t per_die) {
                     const int64_t wgs = t * d, resident = wgs < 256 * cap ? wgs : 256 * cap;
-                    const int64_t per_die = (nblk * d + 7) / 8 * mblk;
-                    const int64_t rounds = (per_die + 32 * cap - 1) / (32 * cap);
-                    // uneven slices only with a compute unit to themselves: two four-wavefront workgroups that share one fall
-                    // further behind the model (bf16, 333 x 13824 x 5120 in three: 66.4 us, whole 59.2; 1325 x 4288 x 2368: 43.0, 33.1)
-                    if (!even && cap == 2 && per_die > 32) continue;
+                    const int64_t rounds = (per_die + 32 * cap - 1) >> (cap == 2 ? 6 : 5);
                     const double step = step1 * (cap == 2 && per_die > 32 ? c.shared_unit : 1.0);   // two sharing a unit
-                    const double hbm_step = 3072.0 * (double)g * (double)resident / (double)mblk / c.hbm_tiled;
-                    const double cost = (double)rounds * ((double)((ktiles + d - 1) / d) * (step > hbm_step ? step : hbm_step) + c.round_fixed +
-                                                          (d > 1 ? c.split_fixed + (double)d * slice : 0.0));
-                    if (!even) {
-                        if (uneven_cost == 0.0 || cost < uneven_cost) {
-                            uneven_cost = cost;
-                            uneven_bm = bm;
-                            uneven_split = (int)d;
-                            uneven_gbn = g;
-                        }
-                    } else if (best_cost == 0.0 || cost < best_cost) {
+                    const double hbm_step = hbm_unit * (double)resident;
+                    return (double)rounds * ((double)slice_tiles[d] * (step > hbm_step ? step : hbm_step) + c.round_fixed +
+                                             (d > 1 ? c.split_fixed + (double)d * slice : 0.0));
+                };
+                for (int n = 0; n < evens && (even_d[n] == 1 || t <= kMaxCounters); n++) {
+                    const double cost = cost_of(even_d[n], pairs_per_die(even_d[n]));
+                    if (best_cost == 0.0 || cost < best_cost) {
                         best_cost = cost;
                         p.block_m = bm;
-                        p.split_k = (int)d;
+                        p.split_k = even_d[n];
                         best_gbn = g;
+                    }
+                }
+                for (int n = 0; n < unevens && t <= kMaxCounters; n++) {
+                    const int64_t per_die = pairs_per_die(uneven_d[n]);
+                    // uneven slices only with a compute unit to themselves: two four-wavefront workgroups that share one fall
+                    // further behind the model (bf16, 333 x 13824 x 5120 in three: 66.4 us, whole 59.2; 1325 x 4288 x 2368: 43.0, 33.1)
+                    if (cap == 2 && per_die > 32) break;
+                    const double cost = cost_of(uneven_d[n], per_die);
+                    if (uneven_cost == 0.0 || cost < uneven_cost) {
+                        uneven_cost = cost;
+                        uneven_bm = bm;
+                        uneven_split = uneven_d[n];
+                        uneven_gbn = g;
                     }
                 }
             }
