@@ -281,6 +281,56 @@ __global__ __launch_bounds__(256) void quantize_small_block_kernel(const uint16_
     if (valid) pack_slot<FMT>(v, d, hi, lo, (size_t)nb * ktiles + tk, 16 * g + i);
 }
 
+// Few, long scale blocks: quantize_kernel would give eight rows of them to one compute unit and leave most of the chip idle.
+// There the maxima are taken by a launch of their own, one workgroup per scale, and a second launch rounds one tile per
+// wavefront and reads W again (a W this small comes from the last-level cache).  Bound by the two launches and the length
+// of a row in one workgroup: 64 x 28672 takes 7.7 us (23.8 in quantize_kernel), 512 x 28672 14.2 (24.3), 64 x 262144 23 (201).
+template <int FMT>
+__global__ __launch_bounds__(256) void block_scale_kernel(const uint16_t* __restrict__ Wt, int N, int K, int block,
+                                                          uint16_t* __restrict__ scales)
+{
+    constexpr float kMax = FMT == kE3M1 ? 24.0f : 28.0f;
+    const unsigned groups = (unsigned)(K / block);
+    const unsigned n = blockIdx.x / groups, gb = blockIdx.x % groups;
+    const u32x4* row = reinterpret_cast<const u32x4*>(Wt + (size_t)n * K + (size_t)gb * block);
+    uint32_t mx = 0;
+#pragma unroll 4
+    for (int v = threadIdx.x; v < block / 8; v += 256) {
+        const u32x4 d = row[v];
+#pragma unroll
+        for (int c = 0; c < 4; c++) mx = max_magnitudes(mx, d[c]);
+    }
+    uint32_t m = max(mx & 0xFFFFu, mx >> 16);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off, 64));
+    __shared__ uint32_t smax[4];
+    if ((threadIdx.x & 63) == 0) smax[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        scales[(size_t)gb * N + n] = __builtin_bit_cast(uint16_t, scale_of(max(max(smax[0], smax[1]), max(smax[2], smax[3])), kMax));
+}
+
+template <int FMT>
+__global__ __launch_bounds__(256) void pack_kernel(const uint16_t* __restrict__ Wt, int N, int K, int block,
+                                                   const uint16_t* __restrict__ scales, u32x4* __restrict__ hi,
+                                                   u32x4* __restrict__ lo)
+{
+    const unsigned ktiles = (unsigned)(K / kTile);
+    const unsigned tile = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (tile >= (unsigned)(N / kTile) * ktiles) return;
+    const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
+    const int nb = (int)(tile / ktiles), tk = (int)(tile % ktiles);
+    const uint16_t* p = Wt + ((size_t)nb * kTile + i) * K + (size_t)tk * kTile + g * 8;
+    u32x4 v[8];
+#pragma unroll
+    for (int f = 0; f < 8; f++) v[f] = *reinterpret_cast<const u32x4*>(p + (size_t)(f >> 1) * 16 * K + (f & 1) * 32);
+    Divisor d[4];
+#pragma unroll
+    for (int t = 0; t < 4; t++)
+        d[t] = divisor_of(__builtin_bit_cast(_Float16, scales[(size_t)(tk / (block / kTile)) * N + nb * kTile + t * 16 + i]));
+    pack_slot<FMT>(v, d, hi, lo, tile, lane);
+}
+
 // ------------------------------------------------------------------ plane readers
 // code of element e (0..7) of a fragment, from its two dwords (L already shifted by 4*(f&1))
 // MB = 2: L = the fragment's dword of the 2-bit plane shifted right by 4*(f&1); code s eee mm.
@@ -390,6 +440,12 @@ static void launch_quantize_t(const uint16_t* Wt, int64_t N, int64_t K, int64_t 
                        (int)N, (int)K, (int)block, scales, (u32x4*)hi, (u32x4*)lo);
 }
 
+// Up to 16 units (64 channels x one scale block; quantize_kernel cuts them into 128 work items at most, one to a compute
+// unit) two launches are ahead from 7168 columns on, in every format.  Measured, us (one launch / two): 1024 x 5632 8.4 / 8.8,
+// 1024 x 8192 10.1 / 10.1, 1024 x 11008 13.8 / 11.9, 1024 x 65536 59 / 49, 1536 x 11008 15.7 / 16.2, 2048 x 16384 23.1 / 26.1;
+// five bits: 1024 x 7168 12.6 / 11.1, 1536 x 8192 14.5 / 14.5, 2048 x 11008 21.9 / 22.2.
+static bool few_long_blocks(int64_t units, int64_t block) { return units <= 16 && block > 7168; }
+
 template <int FMT>
 static hipError_t launch_quantize_format(const uint16_t* Wt, int64_t N, int64_t K, int64_t block, void* hi, void* lo,
                                          uint16_t* scales, hipStream_t stream)
@@ -405,6 +461,13 @@ static hipError_t launch_quantize_format(const uint16_t* Wt, int64_t N, int64_t 
         const int64_t units = (N / kTile) * ((K / kTile + 15) / 16);
         hipLaunchKernelGGL((quantize_small_block_kernel<FMT>), dim3((unsigned)((units + 7) / 8 * 32)), dim3(256), 0, stream,
                            Wt, (int)N, (int)K, (int)block, scales, (u32x4*)hi, (u32x4*)lo);
+    } else if (few_long_blocks((N / kTile) * (K / block), block)) {
+        hipLaunchKernelGGL((block_scale_kernel<FMT>), dim3((unsigned)(N * (K / block))), dim3(256), 0, stream, Wt, (int)N, (int)K,
+                           (int)block, scales);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((pack_kernel<FMT>), dim3((unsigned)(((N / kTile) * (K / kTile) + 3) / 4)), dim3(256), 0, stream, Wt,
+                           (int)N, (int)K, (int)block, (const uint16_t*)scales, (u32x4*)hi, (u32x4*)lo);
     } else if (block <= 1024) {
         launch_quantize_t<FMT, 4, 4, 1>(Wt, N, K, block, hi, lo, scales, 4, stream);
     } else if (block <= 2048) {

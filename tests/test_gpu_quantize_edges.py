@@ -42,6 +42,24 @@ def test_more_work_items_than_workgroups(N, K):
     _check("fp6", inputs.weight(N, K, seed=7200 + K, sigma=0.02, outlier_frac=0.001, device=DEV))
 
 
+@pytest.mark.parametrize("fmt", sorted(FORMATS))
+@pytest.mark.parametrize("N,K", [(64, 7168), (64, 7232), (1024, 7232), (1088, 7232), (1024, 28672), (1088, 8256), (1088, 9216),
+                                 (1088, 9280), (1088, 16384), (1088, 16448), (64, 131136)])
+def test_few_long_rows_and_just_too_many_of_them(fmt, N, K):
+    # up to 16 channel blocks of more than 7168 columns: maxima and codes in two launches
+    _check(fmt, inputs.weight(N, K, seed=7150 + N + K, sigma=0.02, outlier_frac=0.001, device=DEV))
+
+
+@pytest.mark.parametrize("N,K,block", [(128, 32768, 8192), (192, 65536, 8192), (64, 65536, 65536)])
+def test_few_long_fine_grained_blocks(N, K, block):
+    W = inputs.weight(N, K, seed=7350 + N, sigma=0.02, outlier_frac=0.001, device=DEV)
+    hi, lo, sc = P.fp6_quantize_pack_fgq(W, block)
+    codes, scales = O.quantize_fgq(to_np16(W), block)
+    hi_o, lo_o = pack_planes(codes)
+    assert np.array_equal(to_np16(sc), scales.T)
+    assert np.array_equal(hi.cpu().numpy(), hi_o) and np.array_equal(lo.cpu().numpy(), lo_o)
+
+
 @pytest.mark.parametrize("block,K", [(64, 64), (64, 1088), (128, 2176), (256, 1280), (512, 1536), (1024, 3072), (2048, 4096)])
 def test_fine_grained_blocks_and_ragged_chunks(block, K):
     N = 192
