@@ -41,6 +41,8 @@
 #include "fp6_internal.hpp"
 #include "fp6_reduce.hpp"
 
+#include <type_traits>
+
 namespace fp6 {
 
 constexpr int kWaveTileBytes = kHiTileBytes + kLoTileBytes;   // 3072: the planes of one 64x64 tile
@@ -295,7 +297,11 @@ __global__ __launch_bounds__(GBN / WN * KW * 64, (GBN == 4 && KW == 1) ? 2 : 1) 
     // right behind it (planes D steps on, activations DX).  The stage numbers are compile-time constants (the loop below
     // is unrolled over a whole period of both rings), so every LDS address is a register plus an immediate - a ring
     // indexed at run time measured 10-20% slower.
-    auto step = [&](int kt, int ux, int uw) {
+    // tail < 0: a step of the steady state.  Otherwise the tail-th of the last steps, for which everything has been issued: the
+    // loads that may be in flight are those of the steps after the next, and the D-th of them has no next step.  (When they
+    // over-fetched like the others, 106 x 3328 x 128 took 4.37 us against 4.18, 226 x 14208 x 1152 in FP5 15.5 against 15.0.)
+    auto step = [&](int kt, int ux, int uw, auto tail) {
+        constexpr int T = decltype(tail)::value;
         TileRaw raw_n[WN];
         half8 x0_n[MT], x1_n[MT];
         half4 sc_n[4];
@@ -306,16 +312,19 @@ __global__ __launch_bounds__(GBN / WN * KW * 64, (GBN == 4 && KW == 1) ? 2 : 1) 
             hints(0x1);
             __builtin_amdgcn_sched_barrier(0);
         }
-        wait_vmcnt<kInFlight>();
-        __syncthreads();
-        issue(min(kt + DX * KW, kt_last), ux, min(kt + D * KW, kt_last), uw);
-        read_planes(raw_n, (uw + 1) % D);
-        read_x(x0_n, (ux + 1) % DX, 0);
-        if (kWhole) {
-            read_x(x1_n, (ux + 1) % DX, 1);
-            if (FGQ) read_scales(sc_n, (uw + 1) % D);
-            mac(raw, x0, 0);
+        constexpr bool more = T < D - 1;          // the tail's last possible step has no successor
+        if constexpr (more) {
+            wait_vmcnt<(T < 0 ? kInFlight : (D - 2 - T) * kLoads)>();
+            __syncthreads();
+            if (T < 0) issue(min(kt + DX * KW, kt_last), ux, min(kt + D * KW, kt_last), uw);
+            read_planes(raw_n, (uw + 1) % D);
+            read_x(x0_n, (ux + 1) % DX, 0);
+            if (kWhole) {
+                read_x(x1_n, (ux + 1) % DX, 1);
+                if (FGQ) read_scales(sc_n, (uw + 1) % D);
+            }
         }
+        if (kWhole) mac(raw, x0, 0);
         mac(raw, x1, 1);
         hints(0x2);
         if (FGQ) {
@@ -333,28 +342,51 @@ __global__ __launch_bounds__(GBN / WN * KW * 64, (GBN == 4 && KW == 1) ? 2 : 1) 
             }
         }
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (more) {
 #pragma unroll
-        for (int c = 0; c < WN; c++) raw[c] = raw_n[c];
+            for (int c = 0; c < WN; c++) raw[c] = raw_n[c];
 #pragma unroll
-        for (int a = 0; a < MT; a++) {
-            x0[a] = x0_n[a];
-            if (kWhole) x1[a] = x1_n[a];
-        }
-        if (FGQ && kWhole) {
+            for (int a = 0; a < MT; a++) {
+                x0[a] = x0_n[a];
+                if (kWhole) x1[a] = x1_n[a];
+            }
+            if (FGQ && kWhole) {
 #pragma unroll
-            for (int t = 0; t < 4; t++) sc4[t] = sc_n[t];
+                for (int t = 0; t < 4; t++) sc4[t] = sc_n[t];
+            }
         }
     };
 
     constexpr int P = (D % DX == 0) ? D : D * DX;      // steps after which both rings are back at stage 0
+    constexpr auto steady = std::integral_constant<int, -1>();
     int kt = kt_begin;
-    for (; kt + P * KW <= kt_end; kt += P * KW) {      // steady state: branch-free trips of P steps
+    if constexpr (DX == D) {
+        // steady state: branch-free trips of P steps.  One to P steps are left; their stages have all been issued by then, so
+        // they fetch nothing, and a slice of few k tiles pays for no more stages than its ring has.
+        for (; kt + P * KW < kt_end; kt += P * KW) {
 #pragma unroll
-        for (int u = 0; u < P; u++) step(kt + u * KW, u % DX, u % D);
-    }
+            for (int u = 0; u < P; u++) step(kt + u * KW, u % DX, u % D, steady);
+        }
+        static_assert(P <= 4, "one line below per step");
+        auto last = [&](auto nth) {
+            constexpr int u = decltype(nth)::value;
+            if constexpr (u < P) {
+                if (kt + u * KW < kt_end) step(kt + u * KW, u % DX, u % D, nth);
+            }
+        };
+        last(std::integral_constant<int, 0>());
+        last(std::integral_constant<int, 1>());
+        last(std::integral_constant<int, 2>());
+        last(std::integral_constant<int, 3>());
+    } else {
+        for (; kt + P * KW <= kt_end; kt += P * KW) {
 #pragma unroll
-    for (int u = 0; u < P - 1; u++) {        // the remaining steps
-        if (kt + u * KW < kt_end) step(kt + u * KW, u % DX, u % D);
+            for (int u = 0; u < P; u++) step(kt + u * KW, u % DX, u % D, steady);
+        }
+#pragma unroll
+        for (int u = 0; u < P - 1; u++) {        // the remaining steps
+            if (kt + u * KW < kt_end) step(kt + u * KW, u % DX, u % D, steady);
+        }
     }
     wait_vmcnt<0>();     // the over-fetched ring slots must land before LDS is given back
     __syncthreads();
@@ -391,11 +423,19 @@ __global__ __launch_bounds__(GBN / WN * KW * 64, (GBN == 4 && KW == 1) ? 2 : 1) 
         const int tile = nbw * mblk + mb, ntiles = mblk * nblk;
         if (holds_y) {
             __amdgpu_buffer_rsrc_t win = partial_window(partials + ((size_t)s * ntiles + tile) * kTileRegs, kTileRegs * 16);
-#pragma unroll
-            for (int a = 0; a < MT; a++) {
-                if (m0 + a * 16 >= M) break;              // rows past M: nobody reads them
+            auto store = [&](int a) {
 #pragma unroll
                 for (int t = 0; t < NT; t++) store_partial(win, (a * NT + t) * OUT_THREADS + tid2, acc[a][t]);
+            };
+            if (m0 + BM <= M) {
+#pragma unroll
+                for (int a = 0; a < MT; a++) store(a);
+            } else {
+#pragma unroll
+                for (int a = 0; a < MT; a++) {
+                    if (m0 + a * 16 >= M) break;          // rows past M: nobody reads them
+                    store(a);
+                }
             }
         }
         if (second_launch) return;                        // add_slices_kernel does the rest
