@@ -267,7 +267,17 @@ __global__ __launch_bounds__(GBN / WN * KW * 64, (GBN == 4 && KW == 1) ? 2 : 1) 
     // Issue order, plane layout 2 at 128 rows: an LDS read behind each of the first MFMAs (333 x 13824 x 5120 in bf16:
     // 59.0 us, 63.0 without).  The rest is left to the compiler: that pattern costs bias-shift FP6 5 % (512 x 22016 x 8192:
     // 170.0 us, 162.9 without), and VALU operations grouped behind every MFMA spill at 128 rows and lose 1-2 % below.
+    // The integer re-bias at 128 rows: a few vector operations behind every MFMA, or the scheduler unpacks so far ahead that six
+    // registers are spilled and reloaded inside the loop (512 x 22016 x 8192: 298 us against 340).
     auto hints = [&](int part_of_step) {
+        if (!kWhole && DQ == kIntRebias) {
+            __builtin_amdgcn_sched_group_barrier(0x002, 50, 0);
+#pragma unroll
+            for (int n = 0; n < NT * MT; n++) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+            }
+        }
         if (!kWhole && layout2(FMT)) {
             const int reads = part_of_step == 1 ? MT : 3 * WN + MT;
 #pragma unroll

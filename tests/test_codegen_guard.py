@@ -2,10 +2,9 @@
 
 The tiled kernel's main loop keeps its DMA queue full only as long as the compiler reloads no
 spilled register inside it (it cannot see the inline-assembly loads and drains the queue
-before any scratch access it schedules there).  The 128-row, eight-wavefront kernel sits at the
-register limit: it spills exactly one register, around the loop and not in it.  A change that
-costs it a second spill costs 5 % of the M = 512 benchmark without failing any parity test,
-so the scratch sizes are pinned here."""
+before any scratch access it schedules there).  A spill costs 5 to 14 % without failing any
+parity test (the integer re-bias at 128 rows: six registers, 340 us instead of 298 at
+512 x 22016 x 8192), so every instantiation of the kernel is held to a scratch size of zero."""
 import os
 import re
 import shutil
@@ -32,14 +31,12 @@ def _scratch_sizes(source: str) -> dict:
     return sizes
 
 
+# the FP6 kernels; those of the ablations, fine-grained scales, FP5 and plane layout 2; those of bf16
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
-def test_fp6_tiled_kernels_spill_no_more_than_pinned():
-    sizes = {k: v for k, v in _scratch_sizes("fp6_gemm.hip").items() if "gemm_kernel" in k}
-    assert len(sizes) == 7, sizes
-    for name, scratch in sizes.items():
-        # template arguments <BM, D, WN, DQ, FGQ, FMT, GBN, KW, DX> are mangled as ILi<BM>ELi<D>E...
-        big = "ILi128ELi3ELi1ELi0ELb0ELi6ELi8E" in name
-        assert scratch <= (8 if big else 0), (name, scratch)
+@pytest.mark.parametrize("source,kernels", [("fp6_gemm.hip", 7), ("fp6_gemm_variants.hip", 22), ("fp6_gemm_bf16.hip", 6)])
+def test_tiled_kernels_do_not_spill(source, kernels):
+    sizes = {k: v for k, v in _scratch_sizes(source).items() if "gemm_kernel" in k}
+    assert len(sizes) == kernels and all(v == 0 for v in sizes.values()), sizes
 
 
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
