@@ -273,9 +273,9 @@ typedef struct fp6_plan_info {
     int waves;              /* wavefronts per workgroup                                                */
     int depth;              /* tiles (decode) or stages (gemm) in the prefetch ring                    */
     int half_tiles;         /* decode: 1 = workgroups own 32 channels                                   */
-    int meeting;            /* how K-slices are added: 0 none, 1 through partial sums (by the last workgroup to arrive
-                               or, gemm family with much to add, by a second launch), 2 pairwise slots  */
-    int64_t workgroups;     /* launch grid                                                             */
+    int meeting;            /* how K-slices are added: 0 none, 1 by the last workgroup to arrive at a counter,
+                               2 pairwise slots, 3 by a second launch (gemm family, where there is much to add) */
+    int64_t workgroups;     /* launch grid (of the first launch)                                      */
     size_t workspace_bytes; /* what the matching *_workspace_bytes call returns                        */
 } fp6_plan_info;
 int fp6_linear_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int variant, int split_k,

@@ -233,7 +233,7 @@ def fp6_linear_plan(M: int, N: int, K: int, format: int = FP6_FORMAT_E3M2, block
 def plan_text(plan: dict) -> str:
     """One-line summary of a plan for benchmark rows."""
     fam = "decode" if plan["variant"] == FP6_VARIANT_DECODE else "gemm"
-    meet = ("", " counter", " pairwise")[plan["meeting"]]
+    meet = ("", " counter", " pairwise", " second-launch")[plan["meeting"]]
     if fam == "decode":
         return "decode%s rows%d split%d%s wg%d" % (" half" if plan["half_tiles"] else "", plan["block_m"], plan["split_k"],
                                                    meet, plan["workgroups"])

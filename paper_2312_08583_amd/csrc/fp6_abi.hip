@@ -677,7 +677,7 @@ int fp6_linear_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, 
     info->waves = p.waves;
     info->depth = p.depth;
     info->half_tiles = p.half_tiles;
-    info->meeting = p.split_k == 1 ? 0 : (p.pairwise ? 2 : 1);
+    info->meeting = p.split_k == 1 ? 0 : (p.pairwise ? 2 : (p.second_launch ? 3 : 1));
     if (p.variant == FP6_VARIANT_DECODE) {
         // the grids of launch_decode_t / launch_decode_half_t
         info->width = 1;

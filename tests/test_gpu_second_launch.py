@@ -1,6 +1,7 @@
 """Tiled plans whose K-slices are added by a second launch: row counts that are no multiple of 4 or 16, a last workgroup
 with missing channel blocks, slice counts around the eight that are loaded at a time, every format.  Against the oracle; a
-second call on the same workspace gives the same bits."""
+second call on the same workspace gives the same bits.  The last case stays below the line and is added by the last workgroup
+to arrive."""
 import numpy as np
 import pytest
 import torch
@@ -20,11 +21,18 @@ def _variant(bm, width):
     return B.FP6_VARIANT_GEMM | B.FP6_HINT_BLOCK_M(bm) | B.FP6_HINT_WIDTH(width)
 
 
-@pytest.mark.parametrize("fmt,M,bm,width,split", [("fp6", 97, 128, 4, 3), ("fp6", 130, 128, 8, 9), ("fp6", 33, 64, 4, 8),
-                                                  ("fp6", 31, 32, 8, 24), ("fp5", 101, 64, 4, 6), ("v2", 66, 64, 8, 4),
-                                                  ("bf16", 259, 128, 4, 3), ("fgq", 62, 64, 8, 12)])
-def test_slices_added_by_a_second_launch(fmt, M, bm, width, split):
+FORMATS = {"fp6": B.FP6_FORMAT_E3M2, "fgq": B.FP6_FORMAT_E3M2, "fp5": B.FP6_FORMAT_E3M1, "v2": B.FP6_FORMAT_E3M2_V2,
+           "bf16": B.FP6_FORMAT_E3M2_V2_BF16}
+
+
+@pytest.mark.parametrize("fmt,M,bm,width,split,meeting", [("fp6", 97, 128, 4, 3, 3), ("fp6", 130, 128, 8, 9, 3), ("fp6", 33, 64, 4, 8, 3),
+                                                          ("fp6", 31, 32, 8, 24, 3), ("fp5", 101, 64, 4, 6, 3), ("v2", 66, 64, 8, 4, 3),
+                                                          ("bf16", 259, 128, 4, 3, 3), ("fgq", 62, 64, 8, 12, 3),
+                                                          ("fp6", 201, 32, 4, 4, 1)])
+def test_slices_added_by_a_second_launch(fmt, M, bm, width, split, meeting):
     N, K, block = 9 * 64, 72 * 64, 512
+    plan = P.fp6_linear_plan(M, N, K, format=FORMATS[fmt], block=block if fmt == "fgq" else 0, variant=_variant(bm, width), split_k=split)
+    assert plan["meeting"] == meeting, plan
     W = inputs.weight(N, K, seed=5200 + M, sigma=0.02, outlier_frac=0.001, device=DEV)
     act = inputs.activation_bf16 if fmt == "bf16" else inputs.activation
     X = act(M, K, seed=5300 + M, device=DEV)

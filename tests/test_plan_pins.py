@@ -26,7 +26,7 @@ PLANS = [
     ("cfg3_llama13b", 5120, 5120, 1, "decode half rows16 split1 wg160"),
     ("cfg3_llama13b", 5120, 5120, 8, "decode rows16 split5 counter wg400"),
     ("cfg3_llama13b", 5120, 5120, 32, "decode rows32 split2 counter wg160"),
-    ("cfg3_llama13b", 5120, 5120, 128, "gemm 64x256 split5 counter wg208"),
+    ("cfg3_llama13b", 5120, 5120, 128, "gemm 64x256 split5 second-launch wg208"),
     ("cfg3_llama13b", 13824, 5120, 1, "decode rows16 split1 wg216"),
     ("cfg3_llama13b", 13824, 5120, 8, "decode rows16 split1 wg216"),
     ("cfg3_llama13b", 13824, 5120, 32, "decode rows32 split1 wg216"),
@@ -34,7 +34,7 @@ PLANS = [
     ("cfg3_llama13b", 5120, 13824, 1, "decode rows16 split3 counter wg240"),
     ("cfg3_llama13b", 5120, 13824, 8, "decode rows16 split3 counter wg240"),
     ("cfg3_llama13b", 5120, 13824, 32, "decode rows32 split3 counter wg240"),
-    ("cfg3_llama13b", 5120, 13824, 128, "gemm 64x256 split6 counter wg240"),
+    ("cfg3_llama13b", 5120, 13824, 128, "gemm 64x256 split6 second-launch wg240"),
     ("cfg4_llama70b_mlp", 28672, 8192, 1, "decode rows16 split1 wg448"),
     ("cfg4_llama70b_mlp", 28672, 8192, 16, "decode rows16 split1 wg448"),
     ("cfg4_llama70b_mlp", 28672, 8192, 64, "gemm 64x256 split2 counter wg224"),
@@ -42,8 +42,8 @@ PLANS = [
     ("cfg4_llama70b_mlp", 28672, 8192, 512, "gemm 128x512 split1 wg224"),
     ("cfg4_llama70b_mlp", 8192, 28672, 1, "decode half rows16 split1 wg256"),
     ("cfg4_llama70b_mlp", 8192, 28672, 16, "decode rows16 split2 pairwise wg256"),
-    ("cfg4_llama70b_mlp", 8192, 28672, 64, "gemm 64x256 split7 counter wg224"),
-    ("cfg4_llama70b_mlp", 8192, 28672, 256, "gemm 128x256 k2 split4 counter wg256"),
+    ("cfg4_llama70b_mlp", 8192, 28672, 64, "gemm 64x256 split7 second-launch wg224"),
+    ("cfg4_llama70b_mlp", 8192, 28672, 256, "gemm 128x256 k2 split4 second-launch wg256"),
     ("cfg4_llama70b_mlp", 8192, 28672, 512, "gemm 128x256 k2 split2 counter wg256"),
     ("cfg5_34b_stack", 8192, 8192, 1, "decode half rows16 split1 wg256"),
     ("cfg5_34b_stack", 8192, 8192, 512, "gemm 128x256 k2 split2 counter wg256"),
