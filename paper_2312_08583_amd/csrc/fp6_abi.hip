@@ -68,6 +68,21 @@ static bool uneven_worth_a_look(bool plain, int64_t N, int64_t K)
     return !plain || ktiles % 2 == 1 || (ktiles % 16 != 0 && N * K >= (int64_t)12 << 20);
 }
 
+// A second launch adds the K-slices of the tiled kernel where there is much to add.  The last arriver of a block of Y reads all
+// its slices by itself, at the 40 to 50 GB/s of one compute unit; a second launch spreads that over the chip and costs about
+// 3 us more.  Measured on 1726 plans with three slices and more (us, last arriver / second launch): 100 x 8192 x 28672 in
+// eight slices of 112 KB 81 / 63; 222 x 3584 x 3200, five of 32 KB, 18.2 / 19.9.  With four slices and more the line is at 192 KB
+// a block: above it 3 of 1250 plans are slower (by 8 % at most, 22 % faster on the average), between 128 and 192 KB 17 of 162.
+// Three slices leave less to gain: above 64 KB each 13 of 143 plans are slower (6 % faster on the average); at 64 KB 32 of 68
+// where the layer's partial sums exceed 8 MB (111 x 9408 x 1728 15.9 / 18.8), 2 of 14 where they don't.
+// Two slices: the last arriver reads one only (128 KB each: 112 / 121).
+static bool by_second_launch(int64_t M, int block_m, int64_t gbn, int split_k, int64_t tiles)
+{
+    const int64_t rows = M < block_m ? (M + 15) / 16 * 16 : block_m, slice = rows * 256 * gbn;      // bytes
+    if (split_k != 3) return split_k > 3 && split_k * slice >= 192 * 1024;
+    return slice > 64 * 1024 || (slice == 64 * 1024 && 3 * slice * tiles <= (int64_t)8 << 20);
+}
+
 // Number of K-slices for the decode family where the cost model below does not apply: layers of 256 channel
 // blocks or more at up to 16 rows of X (measured on MI355X at M = 1: no split from 384 blocks on; below, two
 // slices, which meet pairwise - cheaper than any larger number), eight-wavefront workgroups, very short K.
@@ -370,13 +385,7 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
         p.pairwise = variant == FP6_VARIANT_DECODE && fits && (hint_meet ? hint_meet == 2 : p.split_k == 2);
         if (!p.pairwise) {
             p.counters = (int)tiles;
-            // The last arriver of a block of Y reads all its slices by itself, at the 40 GB/s of one compute unit; a second
-            // launch spreads that over the chip and costs about 3 us more.  Measured, us (last arriver / second launch):
-            // 100 x 8192 x 28672 in eight slices of 112 KB 81 / 63; 100 x 5120 x 5120, five of 56 KB 20.4 / 18.2;
-            // 48 x 13824 x 5120, four of 48 KB 22.3 / 21.2; 64 x 5120 x 5120, five of 32 KB 15.4 / 17.0; 512 x 1024 x 8192,
-            // four of 32 KB 22.2 / 25.1.  Two slices: the last arriver reads one only (128 KB each: 112 / 121).
-            const int64_t rows = M < p.block_m ? (M + 15) / 16 * 16 : p.block_m;
-            p.second_launch = variant == FP6_VARIANT_GEMM && p.split_k > 2 && p.split_k * rows * 256 * p.gbn >= 192 * 1024;
+            p.second_launch = variant == FP6_VARIANT_GEMM && by_second_launch(M, p.block_m, p.gbn, p.split_k, tiles);
             p.partial_bytes = (size_t)p.split_k * (size_t)tiles * (size_t)regs_per_tile * 16u;
         }
     }

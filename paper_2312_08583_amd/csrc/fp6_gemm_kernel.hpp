@@ -522,17 +522,19 @@ __global__ __launch_bounds__(GBN / WN * KW * 64, (GBN == 4 && KW == 1) ? 2 : 1) 
     }
 }
 
-// The second launch of a split layer: adds the slices (in slice order) and applies the epilogue.  A wavefront takes four rows
-// of one 64-channel block, 16 lanes a row, so that Y is written as whole 128-byte pieces.  GBN and BM are those of the launch
-// that wrote the partial sums (a block of Y holds them as [row block a][16-channel block t][thread]).
+// The second launch of a split layer: adds the slices (in slice order) and applies the epilogue.  A workgroup takes 16 rows of one
+// 64-channel block: the partial sums of four rows are pieces of 64 bytes, so its four wavefronts share whole cache lines (four
+// neighbouring blocks of the same four rows fetched every line twice: of 1320 plans with 192 KB of partial sums per block of Y
+// and more 88 were slower than with the last arriver, now 36).  A wavefront takes four rows, 16 lanes a row, and writes 128-byte pieces of Y.  GBN and BM are those of the
+// launch that wrote the partial sums (a block of Y holds them as [row block a][16-channel block t][thread]).
 template <bool FGQ, int FMT, int DQ>
 __global__ __launch_bounds__(256) void add_slices_kernel(const float4v* __restrict__ partials, const uint16_t* __restrict__ scales,
                                                          int M, int N, int bm, int gbn, int split_k, uint16_t* __restrict__ Y)
 {
     const int lane = threadIdx.x & 63;
     const int nblocks = N / kTile;
-    const unsigned item = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int nb = (int)(item % (unsigned)nblocks), m = (int)(item / (unsigned)nblocks) * 4 + (lane >> 4);
+    const int nb = (int)(blockIdx.x % (unsigned)nblocks);
+    const int m = (int)(blockIdx.x / (unsigned)nblocks) * 16 + (threadIdx.x >> 6) * 4 + (lane >> 4);
     if (m >= M) return;
     const int t = (lane >> 2) & 3, g = lane & 3;
     const int mblk = (M + bm - 1) / bm, nblk = (nblocks + gbn - 1) / gbn;
@@ -572,8 +574,7 @@ static hipError_t launch_gemm_t(const LinearPlan& p, const uint16_t* X, int64_t 
     if (p.second_launch) {
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        const int64_t items = (M + 3) / 4 * (N / kTile);
-        hipLaunchKernelGGL((add_slices_kernel<FGQ, FMT, DQ>), dim3((unsigned)((items + 3) / 4)), dim3(256), 0, stream, partials, scales,
+        hipLaunchKernelGGL((add_slices_kernel<FGQ, FMT, DQ>), dim3((unsigned)((M + 15) / 16 * (N / kTile))), dim3(256), 0, stream, partials, scales,
                            (int)M, (int)N, BM, GBN, p.split_k, Y);
     }
     return hipGetLastError();

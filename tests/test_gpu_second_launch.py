@@ -1,7 +1,7 @@
 """Tiled plans whose K-slices are added by a second launch: row counts that are no multiple of 4 or 16, a last workgroup
 with missing channel blocks, slice counts around the eight that are loaded at a time, every format.  Against the oracle; a
-second call on the same workspace gives the same bits.  The last case stays below the line and is added by the last workgroup
-to arrive."""
+second call on the same workspace gives the same bits.  Two cases stay below the lines and are added by the last workgroup
+to arrive: little per block of Y; three slices of 64 KB where all blocks together have much."""
 import numpy as np
 import pytest
 import torch
@@ -28,7 +28,8 @@ FORMATS = {"fp6": B.FP6_FORMAT_E3M2, "fgq": B.FP6_FORMAT_E3M2, "fp5": B.FP6_FORM
 @pytest.mark.parametrize("fmt,M,bm,width,split,meeting", [("fp6", 97, 128, 4, 3, 3), ("fp6", 130, 128, 8, 9, 3), ("fp6", 33, 64, 4, 8, 3),
                                                           ("fp6", 31, 32, 8, 24, 3), ("fp5", 101, 64, 4, 6, 3), ("v2", 66, 64, 8, 4, 3),
                                                           ("bf16", 259, 128, 4, 3, 3), ("fgq", 62, 64, 8, 12, 3),
-                                                          ("fp6", 201, 32, 4, 4, 1)])
+                                                          ("fp6", 201, 32, 4, 4, 1), ("fp6", 1000, 64, 4, 3, 1),
+                                                          ("fp6", 513, 64, 4, 3, 3), ("fp6", 208, 64, 4, 4, 3)])
 def test_slices_added_by_a_second_launch(fmt, M, bm, width, split, meeting):
     N, K, block = 9 * 64, 72 * 64, 512
     plan = P.fp6_linear_plan(M, N, K, format=FORMATS[fmt], block=block if fmt == "fgq" else 0, variant=_variant(bm, width), split_k=split)
