@@ -57,16 +57,24 @@ static constexpr PlanModel kModel = {
     {0.77, 0.993, 1.417}, 0.57, 1.964, {0.528, 1.588, 4.681}, 2.774, 3.216, 4.529e6,
 };
 
-// K-slices of different lengths (by one k tile, or a pair).  K/64 of few divisors has no good even split (52 x 1600 x
-// 21696: 339 = 3 x 113 tiles), so slices that do not divide it are considered, and taken where the model's cost is this
-// fraction of the best even split's or less.  Plain FP6 keeps even slices where K/64 is a multiple of 16, and on layers
-// below 12 M weights unless K/64 is odd: the configured layers keep plans whose split_k a caller can also force.
+// K-slices of different lengths (by one k tile, or a pair): K/64 of few divisors has no good even split (52 x 1600 x 21696:
+// 339 = 3 x 113 tiles).  They are looked at for every format and K, and taken where the model's cost is this fraction of the
+// best even split's or less and the price below agrees.  Measured on 2445 random layers where the first condition holds
+// (751 on the streaming kernel, 1694 on the tiled one; M = 1 ... 2048, N and K from 256 and 512 on, all formats; us, even /
+// uneven): on the average 0.66 and 0.69 of the time (85 x 3712 x 15424 107 / 27), but 14 and 106 of them were slower.
 static constexpr double kUnevenGain = 0.93;
-static bool uneven_worth_a_look(bool plain, int64_t N, int64_t K)
-{
-    const int64_t ktiles = K / FP6_TILE;
-    return !plain || ktiles % 2 == 1 || (ktiles % 16 != 0 && N * K >= (int64_t)12 << 20);
-}
+// Streaming kernel: an unsplit layer does without a meeting, and by less than this (us) it is not beaten by three slices and
+// more (2 x 2496 x 3904 5.7 / 6.3, 1 x 1088 x 2944 4.8 / 5.0); 5 of 734 stay slower, by 6 % at most.
+static constexpr double kUnevenOverUnsplit = 0.6;
+// Tiled kernel: the model's constants rank plans of one kind well, but know neither the second launch nor the faster loops of
+// plane layout 2.  Before uneven slices are taken, both plans are priced with constants fitted to the 3388 measured times
+// (8 % r.m.s.): a launch, the loop of the model by kind of format, partial sums per MB, and their addition - by the last
+// workgroup to arrive, per KB that it reads, or by a second launch and its slices.  24 of 1539 stay slower, and of the 155
+// layers that keep even slices 29 would have gained more than 5 %.
+struct TiledPrice {
+    double launch, loop, loop_layout2, loop_block, second_launch, second_slice, arriver_kb, partial_mb, gain;
+};
+static constexpr TiledPrice kPrice = {3.03, 0.918, 0.719, 1.203, 1.77, 0.087, 0.0204, 0.423, 0.98};
 
 // A second launch adds the K-slices of the tiled kernel where there is much to add.  The last arriver of a block of Y reads all
 // its slices by itself, at the 40 to 50 GB/s of one compute unit; a second launch spreads that over the chip and costs about
@@ -153,7 +161,7 @@ static void plan_small_decode(int64_t M, int64_t nblocks, int64_t ktiles, int ti
             }
         }
     }
-    if (best_uneven < kUnevenGain * best) {
+    if (best_uneven < kUnevenGain * best && (*split_out > 1 || best - best_uneven >= kUnevenOverUnsplit)) {
         *split_out = uneven_split;
         *half_out = uneven_half;
     }
@@ -212,7 +220,7 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
     // four give twice the workgroups where there are few (measured: 40 against 47 us at 32 x 28672 x 8192, 24
     // against 30 us at 512 x 1024 x 8192, 20.7 against 30 us at 128 x 5120 x 5120).  The cost model below chooses.
     const bool plain = format == kE3M2 && !block && !hint_dequant;
-    even_only = even_only || split_k || variant_hints || !uneven_worth_a_look(plain, N, K);
+    even_only = even_only || split_k || variant_hints;
     const bool narrow_ok = !hint_dequant && variant == FP6_VARIANT_GEMM;      // every format but the ablations
     int64_t gbn = hint_gbn ? hint_gbn : 8;
     p.gbn = (int)gbn;
@@ -272,7 +280,10 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
         // ceil(pairs per die x row blocks / (32 or 64)) rounds;
         // a round costs its k tiles at the per-tile time of the workgroup shape (or of the HBM stream, whichever
         // is longer) plus a fixed part that grows with the number of slices the last workgroup of a tile adds up.
-        double best_cost = 0.0, uneven_cost = 0.0;
+        struct Cost {
+            double total, loop, rounds;      // total as the model has it; the loops of all rounds; rounds
+        };
+        Cost best = {0.0, 0.0, 0.0}, uneven = best;
         int uneven_bm = 0, uneven_split = 0;
         int64_t uneven_gbn = 0;
         if (block && hint_bm > 64) return false;        // fine-grained scales: two accumulators per tile
@@ -302,16 +313,17 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
                 auto pairs_per_die = [&](int d) { return ((nblk * d + 7) >> 3) * mblk; };
                 auto cost_of = [&](int d, int64_t per_die) {
                     const int64_t wgs = t * d, resident = wgs < 256 * cap ? wgs : 256 * cap;
-                    const int64_t rounds = (per_die + 32 * cap - 1) >> (cap == 2 ? 6 : 5);
+                    const double rounds = (double)((per_die + 32 * cap - 1) >> (cap == 2 ? 6 : 5));
                     const double step = step1 * (cap == 2 && per_die > 32 ? c.shared_unit : 1.0);   // two sharing a unit
                     const double hbm_step = hbm_unit * (double)resident;
-                    return (double)rounds * ((double)slice_tiles[d] * (step > hbm_step ? step : hbm_step) + c.round_fixed +
-                                             (d > 1 ? c.split_fixed + (double)d * slice : 0.0));
+                    const double loop = (double)slice_tiles[d] * (step > hbm_step ? step : hbm_step);
+                    return Cost{rounds * (loop + c.round_fixed + (d > 1 ? c.split_fixed + (double)d * slice : 0.0)), rounds * loop,
+                                rounds};
                 };
                 for (int n = 0; n < evens && (even_d[n] == 1 || t <= kMaxCounters); n++) {
-                    const double cost = cost_of(even_d[n], pairs_per_die(even_d[n]));
-                    if (best_cost == 0.0 || cost < best_cost) {
-                        best_cost = cost;
+                    const Cost cost = cost_of(even_d[n], pairs_per_die(even_d[n]));
+                    if (best.total == 0.0 || cost.total < best.total) {
+                        best = cost;
                         p.block_m = bm;
                         p.split_k = even_d[n];
                         best_gbn = g;
@@ -322,9 +334,9 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
                     // uneven slices only with a compute unit to themselves: two four-wavefront workgroups that share one fall
                     // further behind the model (bf16, 333 x 13824 x 5120 in three: 66.4 us, whole 59.2; 1325 x 4288 x 2368: 43.0, 33.1)
                     if (cap == 2 && per_die > 32) break;
-                    const double cost = cost_of(uneven_d[n], per_die);
-                    if (uneven_cost == 0.0 || cost < uneven_cost) {
-                        uneven_cost = cost;
+                    const Cost cost = cost_of(uneven_d[n], per_die);
+                    if (uneven.total == 0.0 || cost.total < uneven.total) {
+                        uneven = cost;
                         uneven_bm = bm;
                         uneven_split = uneven_d[n];
                         uneven_gbn = g;
@@ -332,8 +344,18 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
                 }
             }
         }
-        if (best_cost == 0.0) return false;
-        if (uneven_cost > 0.0 && uneven_cost < kUnevenGain * best_cost) {
+        if (best.total == 0.0) return false;
+        auto price = [&](const Cost& x, int bm, int64_t g, int d) {
+            const int64_t mblk = (M + bm - 1) / bm, nblk = (nblocks + g - 1) / g;
+            const double slice_kb = (double)((M < bm ? (M + 15) / 16 * 16 : bm) * g) * 0.25;          // of one block of Y
+            const double loop = x.loop * (layout2(format) ? kPrice.loop_layout2 : block ? kPrice.loop_block : kPrice.loop);
+            if (d == 1) return kPrice.launch + loop;
+            return kPrice.launch + loop + kPrice.partial_mb * slice_kb * (double)(d * mblk * nblk) / 1024.0 +
+                   (by_second_launch(M, bm, g, d, mblk * nblk) ? kPrice.second_launch + kPrice.second_slice * (double)d
+                                                               : kPrice.arriver_kb * slice_kb * (double)(d > 2 ? d : 1) * x.rounds);
+        };
+        if (uneven.total > 0.0 && uneven.total < kUnevenGain * best.total &&
+            price(uneven, uneven_bm, uneven_gbn, uneven_split) < kPrice.gain * price(best, p.block_m, best_gbn, p.split_k)) {
             p.block_m = uneven_bm;
             p.split_k = uneven_split;
             best_gbn = uneven_gbn;

@@ -105,7 +105,12 @@ def test_plan_query_agrees_with_the_calls_it_describes():
                 p = B.fp6_linear_plan(M, N, K)
                 assert p["workspace_bytes"] == B.fp6_linear_workspace_bytes(M, N, K)
                 assert p["variant"] in (B.FP6_VARIANT_DECODE, B.FP6_VARIANT_GEMM)
-                assert p["split_k"] >= 1 and (K // 64) % p["split_k"] == 0
+                assert 1 <= p["split_k"] <= K // 64
+                if (K // 64) % p["split_k"] == 0:             # a caller can force it too
+                    assert B.fp6_linear_plan(M, N, K, split_k=p["split_k"])["split_k"] == p["split_k"]
+                else:                                         # slices that differ by a k tile: the planner's own
+                    with pytest.raises(B.Fp6Error):
+                        B.fp6_linear_plan(M, N, K, split_k=p["split_k"])
                 assert (p["meeting"] == 0) == (p["split_k"] == 1)
                 assert (p["workspace_bytes"] == 0) == (p["split_k"] == 1)
                 assert p["workgroups"] >= 1

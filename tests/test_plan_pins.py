@@ -54,7 +54,7 @@ PLANS = [
     ("cfg5_34b_stack", 8192, 22016, 1, "decode half rows16 split1 wg256"),
     ("cfg5_34b_stack", 8192, 22016, 512, "gemm 128x256 k2 split2 counter wg256"),
     ("paper_table_b1", 5504, 2048, 8, "decode rows16 split2 pairwise wg172"),
-    ("paper_table_b1", 2048, 5504, 8, "decode rows16 split2 pairwise wg64"),
+    ("paper_table_b1", 2048, 5504, 8, "decode rows16 split6 counter wg192"),
     ("paper_table_b1", 13824, 5120, 8, "decode rows16 split1 wg216"),
     ("paper_table_b1", 5120, 13824, 8, "decode rows16 split3 counter wg240"),
     ("paper_table_b1", 22016, 8192, 8, "decode rows16 split2 pairwise wg688"),
