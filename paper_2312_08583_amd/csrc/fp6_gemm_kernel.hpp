@@ -34,7 +34,8 @@
 // others); where K is split, the meeting of the slices costs another 5-12 % at M = 512.
 //
 // The row scale is applied once, after the accumulation (Section 5.2).  K may be split
-// over workgroups; the slices meet in an fp32 workspace exactly as in the decode kernel.
+// over workgroups; the slices meet in an fp32 workspace and are added by the workgroup that arrives last, as in
+// the decode kernel, or by a second launch.
 #pragma once
 
 #include "fp6_common.hpp"
@@ -502,20 +503,10 @@ __global__ __launch_bounds__(GBN / WN * KW * 64, (GBN == 4 && KW == 1) ? 2 : 1) 
             if (m < M) {
 #pragma unroll
                 for (int t = 0; t < 4; t++) {
-                    // (the fp16 branch is kept exactly as it was before bf16 came: routed through the same helper as the
-                    // bf16 one, the 128-row eight-wavefront kernel spilled a second register, reloaded it inside the main
-                    // loop, and the config-5 stack at M = 512 ran 5 % slower - 35.5 against 33.7 ms on one machine)
-                    if constexpr (FMT == kE3M2B) {
-                        float yv[4];
+                    float yv[4];
 #pragma unroll
-                        for (int r = 0; r < 4; r++) yv[r] = acc[a][c * 4 + t][r] * sc[t][r];
-                        *reinterpret_cast<half4*>(Y + (size_t)m * N + (size_t)nb * kTile + t * 16 + g2 * 4) = to_out4<FMT>(yv);
-                    } else {
-                        half4 y;
-#pragma unroll
-                        for (int r = 0; r < 4; r++) y[r] = (_Float16)(acc[a][c * 4 + t][r] * sc[t][r]);
-                        *reinterpret_cast<half4*>(Y + (size_t)m * N + (size_t)nb * kTile + t * 16 + g2 * 4) = y;
-                    }
+                    for (int r = 0; r < 4; r++) yv[r] = acc[a][c * 4 + t][r] * sc[t][r];
+                    *reinterpret_cast<half4*>(Y + (size_t)m * N + (size_t)nb * kTile + t * 16 + g2 * 4) = to_out4<FMT>(yv);
                 }
             }
         }
@@ -525,8 +516,9 @@ __global__ __launch_bounds__(GBN / WN * KW * 64, (GBN == 4 && KW == 1) ? 2 : 1) 
 // The second launch of a split layer: adds the slices (in slice order) and applies the epilogue.  A workgroup takes 16 rows of one
 // 64-channel block: the partial sums of four rows are pieces of 64 bytes, so its four wavefronts share whole cache lines (four
 // neighbouring blocks of the same four rows fetched every line twice: of 1320 plans with 192 KB of partial sums per block of Y
-// and more 88 were slower than with the last arriver, now 36).  A wavefront takes four rows, 16 lanes a row, and writes 128-byte pieces of Y.  GBN and BM are those of the
-// launch that wrote the partial sums (a block of Y holds them as [row block a][16-channel block t][thread]).
+// and more 88 were slower than with the last arriver, now 36).  A wavefront takes four rows, 16 lanes a row, and writes
+// 128-byte pieces of Y.  GBN and BM are those of the launch that wrote the partial sums (a block of Y holds them as
+// [row block a][16-channel block t][thread]).
 template <bool FGQ, int FMT, int DQ>
 __global__ __launch_bounds__(256) void add_slices_kernel(const float4v* __restrict__ partials, const uint16_t* __restrict__ scales,
                                                          int M, int N, int bm, int gbn, int split_k, uint16_t* __restrict__ Y)
