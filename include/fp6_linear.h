@@ -66,7 +66,7 @@ typedef enum {
     FP6_ERR_NULL = -1,       /* a required pointer is NULL                                  */
     FP6_ERR_SHAPE = -2,      /* M, N or K not positive, or N, K not multiples of FP6_TILE    */
     FP6_ERR_ALIGN = -3,      /* a buffer pointer is not 16-byte aligned                      */
-    FP6_ERR_WORKSPACE = -4,  /* workspace missing or smaller than fp6_linear_workspace_bytes */
+    FP6_ERR_WORKSPACE = -4,  /* workspace missing or too small for every plan of the call    */
     FP6_ERR_VARIANT = -5,    /* kernel variant / split request not valid for this shape      */
     FP6_ERR_HIP = -6,        /* the HIP runtime reported a launch error                      */
     FP6_ERR_SCRATCH = -7     /* fp6_linear_static: the shape needs more than its built-in scratch */
@@ -125,10 +125,13 @@ int fp6_dequantize(const void *hi_plane, const void *lo_plane, const uint16_t *s
                    int64_t N, int64_t K, uint16_t *W_hat, void *stream);
 
 /*
- * Bytes of device workspace fp6_linear may need for this shape (0 is possible).  When K
+ * Bytes of device workspace of fp6_linear's plan for this shape (0 is possible).  When K
  * is cut into slices handled by different workgroups, the workspace is where the slices'
  * fp32 partial sums meet: small ones pairwise in 64-bit slots, large ones through a
- * buffer guarded by one arrival counter per output tile.  CONTRACT: the first
+ * buffer, guarded by one arrival counter per output tile or read by a second launch.  Slices
+ * need not be equally long.  With a workspace that is smaller than this, but large enough for
+ * equal slices (which may need less, or none), a call runs equal slices: the same sum in
+ * another order, and possibly several times slower.  CONTRACT: the first
  * FP6_WORKSPACE_ZERO_BYTES bytes (counters and slots) must be zero before the first call
  * that uses the workspace; every call leaves them zero again, so one buffer can be reused
  * by successive calls on the same stream, whatever their shapes.  Calls that share a
@@ -145,7 +148,8 @@ size_t fp6_linear_workspace_bytes(int64_t M, int64_t N, int64_t K);
  *   X         in  device, fp16 bits [M,K] row-major
  *   hi_plane, lo_plane, scales  in  device, as written by fp6_quantize_pack
  *   Y         out device, fp16 bits [M,N] row-major
- *   workspace     device, >= fp6_linear_workspace_bytes(M,N,K) bytes (may be NULL if that is 0)
+ *   workspace     device, >= fp6_linear_workspace_bytes(M,N,K) bytes (may be NULL if that is 0);
+ *                 with less see there, FP6_ERR_WORKSPACE where equal slices don't fit either
  * Nothing is clamped and nothing is checked for finiteness: a result beyond the fp16 range is
  * stored as an infinity, an infinite or NaN activation propagates through its row of Y by the
  * rules of IEEE arithmetic (inf * 0 and inf - inf give NaN), other rows are not affected.
@@ -157,13 +161,14 @@ int fp6_linear(const uint16_t *X, int64_t M, const void *hi_plane, const void *l
 /*
  * fp6_linear for callers that cannot hand over, or allocate, a workspace: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same computation, same kernels and
- * same results as fp6_linear(X, M, ..., Y, workspace, ...); the K-slices meet in
+ * same results as fp6_linear(X, M, ..., Y, workspace, FP6_STATIC_SCRATCH_BYTES, ...); the K-slices meet in
  * FP6_STATIC_SCRATCH_BYTES (64 MiB) of device memory that belongs to the library: a static device
  * array, one copy per GPU the library is used on, held until the process ends.  The call allocates
  * and frees nothing and never synchronises.
- *   - A shape whose plan needs more scratch than that returns FP6_ERR_SCRATCH before anything is
- *     launched (the need is what fp6_linear_workspace_bytes reports; e.g. M = 512 with K split four
- *     ways over 8192 output channels does not fit): use fp6_linear with a workspace there.
+ *   - Where fp6_linear_workspace_bytes reports more than that, equal K-slices are run if they fit (as
+ *     fp6_linear does with a workspace of this size); otherwise FP6_ERR_SCRATCH is returned before
+ *     anything is launched (e.g. M = 512 with K split four ways over 8192 output channels): use
+ *     fp6_linear with a workspace there.
  *   - All calls on one GPU share that GPU's scratch, which keeps what the last call left: the
  *     counters and slots at its start are cleared by the first call on a device (a small fill kernel
  *     on `stream`, ahead of the first launch) and left zero by every call, the partial sums are
@@ -190,7 +195,8 @@ int fp6_linear_static(const uint16_t *X, int64_t M, const void *hi_plane, const 
  *   problems   host array of `count` (1 .. FP6_GROUP_MAX) descriptions, read during the call only;
  *              every pointer inside is a device pointer with the meaning it has in fp6_linear
  *   workspace  device, >= fp6_linear_group_workspace_bytes(M, problems, count) bytes; same contract
- *              as for fp6_linear (first FP6_WORKSPACE_ZERO_BYTES zero before first use, left zero)
+ *              as for fp6_linear (first FP6_WORKSPACE_ZERO_BYTES zero before first use, left zero;
+ *              with less, equal slices where they fit)
  * Errors as fp6_linear, found on the host before anything is launched; FP6_ERR_SHAPE also for a count
  * outside 1 .. FP6_GROUP_MAX.
  */
@@ -267,7 +273,7 @@ int fp6_linear_variant(const uint16_t *X, int64_t M, const void *hi_plane, const
 typedef struct fp6_plan_info {
     int variant;            /* FP6_VARIANT_DECODE or FP6_VARIANT_GEMM                                   */
     int split_k;            /* K-slices handled by separate workgroups (1 = K is not split); slices of an
-                             * automatic plan may differ by a k tile or two, forced ones may not      */
+                               automatic plan may differ by a k tile or two, forced ones may not      */
     int block_m;            /* rows of X per workgroup: gemm 32/64/128; decode 16, 32 or 64             */
     int width;              /* 64-channel blocks per workgroup: gemm 8 or 4; decode 1                   */
     int waves;              /* wavefronts per workgroup                                                */

@@ -491,7 +491,7 @@ static int quantize_pack_any(int format, const uint16_t* W, int64_t N, int64_t K
 {
     if (!W || !hi_plane || !lo_plane || !scales) return FP6_ERR_NULL;
     if (!shape_ok(N, K) || (block && !block_ok(K, block))) return FP6_ERR_SHAPE;
-    if (block && N * (K / block) > ((int64_t)1 << 30)) return FP6_ERR_SHAPE;      // one workgroup per scale
+    if (block && N * (K / block) > ((int64_t)1 << 30)) return FP6_ERR_SHAPE;      // (scales are counted in 32 bits)
     if (!aligned16(W) || !aligned16(hi_plane) || !aligned16(lo_plane) || !aligned16(scales)) return FP6_ERR_ALIGN;
     forget_earlier_errors();
     return launch_quantize_pack(format, W, N, K, block ? block : K, hi_plane, lo_plane, scales, (hipStream_t)stream) ==

@@ -125,3 +125,19 @@ def test_uneven_slices_on_the_static_scratch(M, N, K):
         Y = P.fp6_linear_static(*layer)
         assert_y_close(Y, Yref, (M, N, K))
     assert torch.equal(Y, P.fp6_linear(*layer))
+
+
+@pytest.mark.gpu
+def test_equal_slices_where_uneven_ones_exceed_the_static_scratch():
+    M, N, K = 2020, 2176, 6464
+    assert P.fp6_linear_workspace_bytes(M, N, K) > P.FP6_STATIC_SCRATCH_BYTES
+    assert (K // 64) % P.fp6_linear_plan(M, N, K)["split_k"] != 0
+    W = inputs.weight(N, K, seed=7500, sigma=0.02, outlier_frac=0.001, device=DEV)
+    X = inputs.activation(M, K, seed=7501, device=DEV)
+    planes = P.fp6_quantize_pack(W)
+    Y = P.fp6_linear_static(X, *planes, N, K)
+    assert torch.equal(Y, P.fp6_linear(X, *planes, N, K, workspace=P.new_workspace(P.FP6_STATIC_SCRATCH_BYTES, DEV)))
+    rows = [0, 127, 128, 1000, M - 1]          # a row of Y depends on its row of X only
+    _, _, Yref = oracle_reference(W, X[rows])
+    assert_y_close(Y[rows], Yref, (M, N, K))
+    assert_y_close(P.fp6_linear(X, *planes, N, K)[rows], Yref, (M, N, K))
