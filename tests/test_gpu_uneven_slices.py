@@ -141,3 +141,14 @@ def test_equal_slices_where_uneven_ones_exceed_the_static_scratch():
     _, _, Yref = oracle_reference(W, X[rows])
     assert_y_close(Y[rows], Yref, (M, N, K))
     assert_y_close(P.fp6_linear(X, *planes, N, K)[rows], Yref, (M, N, K))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dequant", [1, 2])
+@pytest.mark.parametrize("M,N,K", [(8, 1088, 101 * 64), (130, 1152, 73 * 64)])
+def test_ablations_on_uneven_slices(M, N, K, dequant):
+    variant = B.FP6_HINT_DEQUANT(dequant)
+    assert (K // 64) % P.fp6_linear_plan(M, N, K, variant=variant)["split_k"] != 0
+    (layer,), (Yref,) = _fp6_layers(M, [(N, K)], seed=7600 + M)
+    X, hi, lo, sc, N, K = layer
+    assert_y_close(P.fp6_linear_variant(X, hi, lo, sc, N, K, variant), Yref, (M, N, K, dequant))

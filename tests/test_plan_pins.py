@@ -84,3 +84,11 @@ def test_plan_of_grouped_layers(M, shapes, plan):
     n_total, K = sum(N for N, _ in shapes), shapes[0][1]
     assert P.plan_text(P.fp6_linear_plan(M, n_total, K)) == plan
     assert P.fp6_linear_group_workspace_bytes(M, shapes) == P.fp6_linear_plan(M, n_total, K)["workspace_bytes"]
+
+
+@pytest.mark.parametrize("dequant", [1, 2])
+@pytest.mark.parametrize("N,K", [(N, K) for wl, N, K, M, _ in PLANS if wl == "paper_table_b1" and M == 8] + [(1088, 101 * 64)])
+def test_the_ablations_are_planned_like_the_method(N, K, dequant):
+    """Bias shift and ablations are timed against each other at batch 8: the unpack is to be the only difference."""
+    method = P.fp6_linear_plan(8, N, K)
+    assert P.fp6_linear_plan(8, N, K, variant=P.binding.FP6_HINT_DEQUANT(dequant)) == method
