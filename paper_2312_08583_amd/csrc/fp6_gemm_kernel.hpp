@@ -18,18 +18,19 @@
 //   - each wavefront's own 3 KB of packed planes per block of output channels
 //     (lane-linear, exactly the order the planes have in memory).
 // The DMA is issued from inline assembly and waited for with explicit s_waitcnt vmcnt:
-// every step issues the same number of loads per wavefront, so "at most (D-2) groups
-// still in flight" is a constant, and the compiler (which cannot see these loads) has
+// every step but the last ones issues the same number of loads per wavefront, so "at most (D-2)
+// groups still in flight" is a constant, and the compiler (which cannot see these loads) has
 // no reason to drain the queue.  One barrier per k tile publishes the next step's stage and
 // frees this step's, whose operands are in registers by then (see step()).
 //
 // LDS traffic per k tile: every wavefront reads the whole X slice (wavefronts x BM x 128 B) plus its
 // planes - at BM = 128 about 152 KB per 2048 MFMA cycles of a SIMD, some 60 % of the 128 B/clk port.
-// Measured (before a step's operands were read ahead of its barrier, which gave 1-2 % at 128 rows in fp16, 13 % in bf16,
-// 5-9 % on row counts between 64 and 1300), the loop keeps the matrix pipe busy 40-50 % of the time at BM = 128 and less at smaller BM,
-// where a k tile holds too few MFMAs per barrier.  With the loads, the barrier, the unpack or the X
-// reads taken out one at a time the loop gets no more than 10 % faster, and with all of them out 18 %:
-// no single stage is the limit.  The shader clock under this kernel stays at 2.1-2.4 GHz of 2.4 on
+// Measured at M = 512, the kernel keeps the matrix pipe of a busy compute unit occupied 59 % (22016 x 8192, 172 units
+// busy), 54 % (8192 x 22016) and 41 % (8192 x 8192, two slices) of the time, and less at smaller BM, where a k tile
+// holds too few MFMAs per barrier.  (58, 51 and 39 % before a step's operands were read ahead of its barrier, which gave
+// 1-2 % at 128 rows in fp16, 13 % in bf16, 5-9 % on row counts between 64 and 1300.)  On that earlier loop, with the
+// loads, the barrier, the unpack or the X reads taken out one at a time it got no more than 10 % faster, and with all
+// of them out 18 %: no single stage is the limit.  The shader clock under this kernel stays at 2.1-2.4 GHz of 2.4 on
 // random data (zeros run up to 20 % faster on the shapes that fill all CUs, hardly at all on the
 // others); where K is split, the meeting of the slices costs another 5-12 % at M = 512.
 //
