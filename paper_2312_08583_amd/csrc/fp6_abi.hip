@@ -81,14 +81,15 @@ static constexpr TiledPrice kPrice = {3.03, 0.918, 0.719, 1.203, 1.77, 0.087, 0.
 // 3 us more.  Measured on 1726 plans with three slices and more (us, last arriver / second launch): 100 x 8192 x 28672 in
 // eight slices of 112 KB 81 / 63; 222 x 3584 x 3200, five of 32 KB, 18.2 / 19.9.  With four slices and more the line is at 192 KB
 // a block: above it 3 of 1250 plans are slower (by 8 % at most, 22 % faster on the average), between 128 and 192 KB 17 of 162.
-// Three slices leave less to gain: above 64 KB each 13 of 143 plans are slower (6 % faster on the average); at 64 KB 32 of 68
-// where the layer's partial sums exceed 8 MB (111 x 9408 x 1728 15.9 / 18.8), 2 of 14 where they don't.
+// Three slices leave less to gain: above 64 KB each 13 of 143 plans are slower (6 % faster on the average); at 64 KB 59 of 116
+// where the second launch has more than 6 MB to read (111 x 9408 x 1728 15.9 / 18.8), 2 of 35 where it has less (12 % faster on
+// the average; 4041 x 64 x 1728, where it skips the channel blocks that the workgroups have past N, 22.6 / 16.9).
 // Two slices: the last arriver reads one only (128 KB each: 112 / 121).
-static bool by_second_launch(int64_t M, int block_m, int64_t gbn, int split_k, int64_t tiles)
+static bool by_second_launch(int64_t M, int64_t N, int block_m, int64_t gbn, int split_k)
 {
     const int64_t rows = M < block_m ? (M + 15) / 16 * 16 : block_m, slice = rows * 256 * gbn;      // bytes
     if (split_k != 3) return split_k > 3 && split_k * slice >= 192 * 1024;
-    return slice > 64 * 1024 || (slice == 64 * 1024 && 3 * slice * tiles <= (int64_t)8 << 20);
+    return slice > 64 * 1024 || (slice == 64 * 1024 && 3 * M * N * 4 <= (int64_t)6 << 20);
 }
 
 // Number of K-slices for the decode family where the cost model below does not apply: layers of 256 channel
@@ -352,7 +353,7 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
             const double loop = x.loop * (layout2(format) ? kPrice.loop_layout2 : block ? kPrice.loop_block : kPrice.loop);
             if (d == 1) return kPrice.launch + loop;
             return kPrice.launch + loop + kPrice.partial_mb * slice_kb * (double)(d * mblk * nblk) / 1024.0 +
-                   (by_second_launch(M, bm, g, d, mblk * nblk) ? kPrice.second_launch + kPrice.second_slice * (double)d
+                   (by_second_launch(M, N, bm, g, d) ? kPrice.second_launch + kPrice.second_slice * (double)d
                                                                : kPrice.arriver_kb * slice_kb * (double)(d > 2 ? d : 1) * x.rounds);
         };
         if (uneven.total > 0.0 && uneven.total < kUnevenGain * best.total &&
@@ -408,7 +409,7 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
         p.pairwise = variant == FP6_VARIANT_DECODE && fits && (hint_meet ? hint_meet == 2 : p.split_k == 2);
         if (!p.pairwise) {
             p.counters = (int)tiles;
-            p.second_launch = variant == FP6_VARIANT_GEMM && by_second_launch(M, p.block_m, p.gbn, p.split_k, tiles);
+            p.second_launch = variant == FP6_VARIANT_GEMM && by_second_launch(M, N, p.block_m, p.gbn, p.split_k);
             p.partial_bytes = (size_t)p.split_k * (size_t)tiles * (size_t)regs_per_tile * 16u;
         }
     }

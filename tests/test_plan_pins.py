@@ -92,3 +92,10 @@ def test_the_ablations_are_planned_like_the_method(N, K, dequant):
     """Bias shift and ablations are timed against each other at batch 8: the unpack is to be the only difference."""
     method = P.fp6_linear_plan(8, N, K)
     assert P.fp6_linear_plan(8, N, K, variant=P.binding.FP6_HINT_DEQUANT(dequant)) == method
+
+
+@pytest.mark.parametrize("M,N,K,meeting", [(4041, 64, 1728, 3), (2730, 192, 1728, 3), (2731, 192, 1728, 1), (111, 9408, 1728, 1)])
+def test_three_slices_of_64_kb_meet_by_what_is_to_read(M, N, K, meeting):
+    """Up to 6 MB of partial sums within N go to a second launch; those of the channel blocks past N don't count."""
+    v = P.binding.FP6_VARIANT_GEMM | P.binding.FP6_HINT_BLOCK_M(64) | P.binding.FP6_HINT_WIDTH(4)
+    assert P.fp6_linear_plan(M, N, K, variant=v, split_k=3)["meeting"] == meeting
