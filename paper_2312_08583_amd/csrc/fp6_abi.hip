@@ -74,6 +74,14 @@ static constexpr double kUnevenOverUnsplit = 0.6;
 struct TiledPrice {
     double launch, loop, loop_layout2, loop_block, second_launch, second_slice, arriver_kb, partial_mb, gain;
 };
+// The model also charges too little for last arrivers that finish together and share what their dies can read (2048 x 512 x
+// 1024 in four slices, 128 last arrivers: storing and adding the sums takes 9 us, 4.3 in the model).  A plan of four-wavefront
+// workgroups of up to 64 rows that is split evenly and added by them therefore gives way to the best unsplit one of that kind
+// where this is priced at the fraction below or less.  Of 328 random layers that it changes one is slower (by 1.7 %), 18 % faster
+// on the average (2048 x 512 x 1024 18.0 / 13.4 us); from 0.9 to 0.95 13 of 94 are.  Left out, because 11 of 24 are slower:
+// fine-grained scales (135 x 14080 x 2880 34.7 / 41.4) and two slices whose unsplit plan has more rows (206 x 8256 x 2432 in bf16
+// 18.9 / 21.2).  Of wider workgroups and 128 rows half would lose.
+static constexpr double kWholeGain = 0.9;
 static constexpr TiledPrice kPrice = {3.03, 0.918, 0.719, 1.203, 1.77, 0.087, 0.0204, 0.423, 0.98};
 
 // A second launch adds the K-slices of the tiled kernel where there is much to add.  The last arriver of a block of Y reads all
@@ -285,9 +293,9 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
         struct Cost {
             double total, loop, rounds;      // total as the model has it; the loops of all rounds; rounds
         };
-        Cost best = {0.0, 0.0, 0.0}, uneven = best;
-        int uneven_bm = 0, uneven_split = 0;
-        int64_t uneven_gbn = 0;
+        Cost best = {0.0, 0.0, 0.0}, uneven = best, whole = best;      // whole: the best unsplit one
+        int uneven_bm = 0, uneven_split = 0, whole_bm = 0;
+        int64_t uneven_gbn = 0, whole_gbn = 0;
         if (block && hint_bm > 64) return false;        // fine-grained scales: two accumulators per tile
         int64_t best_gbn = gbn;
         // the numbers of slices to look at, even and uneven ones, and the k tiles of their longest slice (ktiles <= 2^24)
@@ -330,6 +338,11 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
                         p.split_k = even_d[n];
                         best_gbn = g;
                     }
+                    if (even_d[n] == 1 && (whole.total == 0.0 || cost.total < whole.total)) {
+                        whole = cost;
+                        whole_bm = bm;
+                        whole_gbn = g;
+                    }
                 }
                 for (int n = 0; n < unevens && t <= kMaxCounters; n++) {
                     const int64_t per_die = pairs_per_die(uneven_d[n]);
@@ -361,6 +374,11 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
             p.block_m = uneven_bm;
             p.split_k = uneven_split;
             best_gbn = uneven_gbn;
+        } else if (p.split_k > 1 && whole.total > 0.0 && !block && (p.split_k > 2 || whole_bm <= p.block_m) && p.block_m <= 64 &&
+                   best_gbn == 4 && whole_bm <= 64 && whole_gbn == 4 && !by_second_launch(M, N, p.block_m, best_gbn, p.split_k) &&
+                   price(whole, whole_bm, whole_gbn, 1) <= kWholeGain * price(best, p.block_m, best_gbn, p.split_k)) {
+            p.block_m = whole_bm;
+            p.split_k = 1;
         }
         const bool even = ktiles % p.split_k == 0;
         gbn = best_gbn;
