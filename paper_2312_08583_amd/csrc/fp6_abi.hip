@@ -64,8 +64,13 @@ static constexpr PlanModel kModel = {
 // uneven): on the average 0.66 and 0.69 of the time (85 x 3712 x 15424 107 / 27), but 14 and 106 of them were slower.
 static constexpr double kUnevenGain = 0.93;
 // Streaming kernel: an unsplit layer does without a meeting, and by less than this (us) it is not beaten by three slices and
-// more (2 x 2496 x 3904 5.7 / 6.3, 1 x 1088 x 2944 4.8 / 5.0); 5 of 734 stay slower, by 6 % at most.
-static constexpr double kUnevenOverUnsplit = 0.6;
+// more (2 x 2496 x 3904 5.7 / 6.3, 1 x 1088 x 2944 4.8 / 5.0).  96 and more half-tile workgroups of FP5 are faster than the model has
+// them (1 x 4608 x 5056 6.7 / 7.4): by less than 1.6 us 7 of 13 such layers were slower in uneven slices, above none of 21.
+static constexpr double kUnevenOverUnsplit = 0.6, kUnevenOverUnsplitFp5Half = 1.6;
+// Nor is it beaten by more workgroups than the chip has compute units, up to 4 rows of X with scales per row in plane layout 1, while
+// the planes take no longer than this (us) to stream: the model has 129 to 143 unsplit workgroups too slow (1 x 8320 x 9344: 13.4 us,
+// 15.2 in three slices).  Of 170 such layers 110 were slower by more than 3 %, all by 5 % on the average; above it 7 of 133, and 3.5 % faster.
+static constexpr double kUnevenManyStream = 14.0;
 // Tiled kernel: the model's constants rank plans of one kind well, but know neither the second launch nor the faster loops of
 // plane layout 2.  Before uneven slices are taken, both plans are priced with constants fitted to the 3388 measured times
 // (8 % r.m.s.): a launch, the loop of the model by kind of format, partial sums per MB, and their addition - by the last
@@ -170,7 +175,10 @@ static void plan_small_decode(int64_t M, int64_t nblocks, int64_t ktiles, int ti
             }
         }
     }
-    if (best_uneven < kUnevenGain * best && (*split_out > 1 || best - best_uneven >= kUnevenOverUnsplit)) {
+    const double over = *half_out && tile_bytes != 3072 && 2 * nblocks >= 96 ? kUnevenOverUnsplitFp5Half : kUnevenOverUnsplit;
+    const bool many = may_half && nblocks * uneven_split * (uneven_half ? 2 : 1) > 256 && stream < kUnevenManyStream;
+    const bool stays_whole = *split_out == 1 && (many || best - best_uneven < over);
+    if (best_uneven < kUnevenGain * best && !stays_whole) {
         *split_out = uneven_split;
         *half_out = uneven_half;
     }

@@ -37,10 +37,11 @@ def test_the_planner_splits_these_unevenly(fmt, M, N, K):
 
 
 # uneven slices would save little or nothing here (measured, even / uneven: 8.2 / 11.4 us, 9.9 / 13.5, 10.8 / 14.4, 18.2 / 24.3,
-# 10.2 / 11.2; streaming kernel 5.7 / 6.3, 4.8 / 5.0, 7.2 / 7.8)
+# 10.2 / 11.2; streaming kernel 5.7 / 6.3, 4.8 / 5.0, 7.2 / 7.8, 13.4 / 15.2, 13.2 / 14.5, 6.7 / 7.4)
 @pytest.mark.parametrize("fmt,M,N,K", [("bf16", 483, 576, 1088), ("v2", 64, 4672, 1728), ("fp6", 269, 1024, 1728),
                                        ("fp5", 244, 3136, 3712), ("fp6", 324, 576, 1088), ("fp6", 2, 2496, 3904),
-                                       ("fp6", 1, 1088, 2944), ("fp6", 20, 4352, 1984)])
+                                       ("fp6", 1, 1088, 2944), ("fp6", 20, 4352, 1984), ("fp6", 1, 8320, 9344),
+                                       ("fp6", 3, 8768, 8384), ("fp5", 1, 4608, 5056)])
 def test_the_planner_leaves_these_even(fmt, M, N, K):
     assert (K // 64) % _plan(fmt, M, N, K)["split_k"] == 0
 
