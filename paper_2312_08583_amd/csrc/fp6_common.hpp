@@ -158,6 +158,33 @@ __device__ __forceinline__ half8 unpack_tile_fragment(const TileRaw& r, int f)
     return unpack_fragment<DQ>(tile_hi_dword(r, f), tile_lo_dword(r, f) >> (4 * (f & 1)));
 }
 
+// The same for the four fragments of k block q of a tile in 32 steps of one to three operations, for a caller that deals them
+// out between MFMAs: step c is part c % 4 (exponents with mantissas, signs, first and second operand register) of group
+// (c / 4) % 2 of fragment 2 * (c / 8) + q.  em, u: what the parts of a group hand on; w[t] = the fragments.
+template <int DQ, int FMT>
+__device__ __forceinline__ void unpack_step(const TileRaw& r, int q, int c, uint32_t& em, uint32_t& u, u32x4 (&w)[4])
+{
+    const int t = c >> 3, f = 2 * t + q, grp = (c >> 2) & 1, part = c & 3;
+    const uint32_t H = tile_hi_dword(r, f);
+    if (part == 0) {
+        uint32_t L;
+        if (FMT == kE3M1) {
+            const int fq = f & 3;
+            L = grp ? r.lo[f >> 2] >> (2 * fq) : (fq ? r.lo[f >> 2] >> (2 * fq - 1) : r.lo[f >> 2] << 1);
+        } else {
+            L = tile_lo_dword(r, f) >> (4 * (f & 1) + 2 * grp);
+        }
+        em = bit_select(grp ? H >> 3 : H, L, 0x1C1C1C1Cu);
+    } else if (part == 1) {
+        u = bit_select(grp ? H << 6 : H << 7, em, 0x80808080u);
+        if (DQ == kIntRebias) u = rebias_bytes(u);
+    } else {
+        constexpr uint32_t kKeep = DQ == kIntRebias ? 0xFF00FF00u : (FMT == kE3M1 ? 0x9E009E00u : 0x9F009F00u);
+        const uint32_t d = (part == 2 ? u << 8 : u) & kKeep;
+        w[t][2 * grp + (part & 1)] = DQ == kHalfMul ? __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2v, d) * (_Float16)4096.0f) : d;
+    }
+}
+
 // ---- plane layout 2 (kE3M2H): merge in registers, convert in hardware ---------------------------
 // A unit = the 32 weights a lane holds for one 32-wide k block of a tile: element i = 8t + e is
 // element e (k = 8 * (lane/16) + e inside the block) of the 16-channel fragment t.  Written as a
@@ -191,28 +218,33 @@ __device__ __forceinline__ u32x6 merge_unit(u32x4 A, uint32_t B0, uint32_t B1)
     return T;
 }
 
-// The four MFMA operands (fragments t = 0..3) of k block q of a tile.
+// The string of k block q of a tile, and its conversion to the four MFMA operands (fragments t = 0..3).  bf16 operands
+// travel in the same 128-bit registers; only the MFMA and the final conversion know.
+__device__ __forceinline__ u32x6 merge_kblock(const TileRaw& r, int q)
+{
+    return merge_unit(q ? r.hi1 : r.hi0, r.lo[2 * q], r.lo[2 * q + 1]);
+}
+
+template <int FMT>
+__device__ __forceinline__ void convert_kblock(u32x6 T, u32x4 (&w)[4])
+{
+    typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
+    u32x16 d;
+    if (FMT == kE3M2B) d = __builtin_bit_cast(u32x16, __builtin_amdgcn_cvt_scalef32_pk32_bf16_bf6(T, 1.0f));
+    else d = __builtin_bit_cast(u32x16, __builtin_amdgcn_cvt_scalef32_pk32_f16_bf6(T, 1.0f));
+#pragma unroll
+    for (int t = 0; t < 4; t++) w[t] = u32x4{d[4 * t], d[4 * t + 1], d[4 * t + 2], d[4 * t + 3]};
+}
+
+// The four MFMA operands of k block q of a tile.
 template <int DQ, int FMT>
 __device__ __forceinline__ void unpack_kblock(const TileRaw& r, int q, half8 (&w)[4])
 {
-    if (FMT == kE3M2H) {
-        const u32x6 T = merge_unit(q ? r.hi1 : r.hi0, r.lo[2 * q], r.lo[2 * q + 1]);
-        const half32 h = __builtin_amdgcn_cvt_scalef32_pk32_f16_bf6(T, 1.0f);
+    if (layout2(FMT)) {
+        u32x4 d[4];
+        convert_kblock<FMT>(merge_kblock(r, q), d);
 #pragma unroll
-        for (int t = 0; t < 4; t++)
-#pragma unroll
-            for (int e = 0; e < 8; e++) w[t][e] = h[8 * t + e];
-    } else if (FMT == kE3M2B) {
-        // bf16 operands travel in the same 128-bit registers; only the MFMA and the final conversion know
-        const u32x6 T = merge_unit(q ? r.hi1 : r.hi0, r.lo[2 * q], r.lo[2 * q + 1]);
-        const bf16x32 h = __builtin_amdgcn_cvt_scalef32_pk32_bf16_bf6(T, 1.0f);
-#pragma unroll
-        for (int t = 0; t < 4; t++) {
-            bf16x8 b;
-#pragma unroll
-            for (int e = 0; e < 8; e++) b[e] = h[8 * t + e];
-            w[t] = __builtin_bit_cast(half8, b);
-        }
+        for (int t = 0; t < 4; t++) w[t] = __builtin_bit_cast(half8, d[t]);
     } else {
 #pragma unroll
         for (int t = 0; t < 4; t++) w[t] = unpack_tile_fragment<DQ, FMT>(r, 2 * t + q);

@@ -3,8 +3,7 @@
 // fp6_gemm_variants.hip: ablations, fine-grained scales, FP5).
 //
 // A workgroup computes a BM x (64 * GBN) block of Y, GBN = 8 or 4.  Its wavefronts stand side by
-// side along N, each owning WN 64-wide blocks of output channels (WN = 1 in every instantiated
-// kernel: one wavefront per 64 channels, two per SIMD at GBN = 8).  Every packed
+// side along N, one per 64 output channels (two per SIMD at GBN = 8).  Every packed
 // weight is fetched and padded to fp16 (bias shift, Section 5.2) by exactly one
 // wavefront and goes straight into MFMA operand registers - the dequantized weight never
 // exists in memory.  Only the activations are shared.
@@ -20,19 +19,21 @@
 // The DMA is issued from inline assembly and waited for with explicit s_waitcnt vmcnt:
 // every step but the last ones issues the same number of loads per wavefront, so "at most (D-2)
 // groups still in flight" is a constant, and the compiler (which cannot see these loads) has
-// no reason to drain the queue.  One barrier per k tile publishes the next step's stage and
-// frees this step's, whose operands are in registers by then (see step()).
+// no reason to drain the queue.  One barrier per k tile publishes the next step's activations and
+// frees this step's, which are in registers by then; planes are a wavefront's own and need none (see step()).
 //
 // LDS traffic per k tile: every wavefront reads the whole X slice (wavefronts x BM x 128 B) plus its
 // planes - at BM = 128 about 152 KB per 2048 MFMA cycles of a SIMD, some 60 % of the 128 B/clk port.
-// Measured at M = 512, the kernel keeps the matrix pipe of a busy compute unit occupied 59 % (22016 x 8192, 172 units
-// busy), 54 % (8192 x 22016) and 41 % (8192 x 8192, two slices) of the time, and less at smaller BM, where a k tile
-// holds too few MFMAs per barrier.  (58, 51 and 39 % before a step's operands were read ahead of its barrier, which gave
-// 1-2 % at 128 rows in fp16, 13 % in bf16, 5-9 % on row counts between 64 and 1300.)  On that earlier loop, with the
-// loads, the barrier, the unpack or the X reads taken out one at a time it got no more than 10 % faster, and with all
-// of them out 18 %: no single stage is the limit.  The shader clock under this kernel stays at 2.1-2.4 GHz of 2.4 on
-// random data (zeros run up to 20 % faster on the shapes that fill all CUs, hardly at all on the
-// others); where K is split, the meeting of the slices costs another 5-12 % at M = 512.
+// What bounds it (cycle counter and wall clock read in the kernel, random data): with every compute unit busy the clock.  A
+// step at 128 x 512 takes 2450 cycles of the 2048 its MFMAs need, at 1.8 GHz (2048 x 8192 x 8192: 1.39 PFLOP/s); without the
+// LDS reads of X it takes 2410, without the DMA or without the unpack 2230, without all three 2070 - and the clock stays at
+// 1.8 to 2.0, where an MFMA-only loop on random operands settles too (1.98 PFLOP/s, 2.44 on zeros).  What costs energy costs
+// time there: 5, 11 and 12 %.  With 172 units busy (512 x 22016 x 8192) the clock is 2.2 GHz.  The vector operations of
+// the unpack hide behind the MFMAs of a SIMD's two wavefronts as long as there are no more than two of them to each, evenly spread:
+// in bursts they cost a quarter (a loop of nothing else: 2640 cycles against 2140).
+// Four-wavefront workgroups with a compute unit to themselves are bound by the instructions one wavefront can issue, one
+// in five cycles or so: 1190 cycles a step at 64 rows (210 instructions, 512 cycles of MFMAs).
+// Where K is split, the meeting of the slices costs another 5-12 % at M = 512.
 //
 // The row scale is applied once, after the accumulation (Section 5.2).  K may be split
 // over workgroups; the slices meet in an fp32 workspace and are added by the workgroup that arrives last, as in
@@ -88,47 +89,45 @@ __device__ __forceinline__ void wait_vmcnt()
 // BM x (64 * GBN) block of Y one k tile further along, so a step covers two k tiles, and the two sets' sums are
 // added in LDS after the main loop.  It is what two workgroups of a two-way K-split would do, with the meeting moved
 // from the workspace into LDS: where K has to be split to fill the chip, half of the partial sums never leave the
-// compute unit.  The ring then has DX stages for the activations (two k tiles each; they come from L2) and D stages
-// for the planes (they come from HBM and need the longer lead).
-template <int BM, int D, int WN, int DQ, bool FGQ, int FMT, int GBN, int KW = 1, int DX = D>
-__global__ __launch_bounds__(GBN / WN * KW * 64, (GBN == 4 && KW == 1) ? 2 : 1) void gemm_kernel(
+// compute unit.
+template <int BM, int D, int DQ, bool FGQ, int FMT, int GBN, int KW>
+__global__ __launch_bounds__(GBN * KW * 64, (GBN == 4 && KW == 1 && BM <= 128) ? 2 : 1) void gemm_kernel(
     const uint16_t* __restrict__ X, int M, const u32x4* __restrict__ hi, const u32x4* __restrict__ lo,
     const uint16_t* __restrict__ scales, int N, int K, uint16_t* __restrict__ Y,
     float4v* __restrict__ partials, uint32_t* __restrict__ counters, int split_k, int gshift, int second_launch)
 {
-    static_assert(!FGQ || (WN == 1 && BM <= 64 && KW == 1), "fine-grained scales: two accumulators must fit the register file");
-    static_assert(KW == 1 || (KW == 2 && WN == 1), "K-ways inside the workgroup: one or two");
-    static_assert(DX >= 2 && DX <= D, "the activations never need a longer lead than the planes");
-    constexpr int NWAVES = GBN / WN;                    // wavefronts side by side along N
-    constexpr int WAVES = NWAVES * KW;
-    constexpr int OUT_THREADS = NWAVES * 64;            // threads that hold the block of Y after the main loop
+    static_assert(!FGQ || BM <= 64, "fine-grained scales: two accumulators must fit the register file");
+    static_assert(KW == 1 || KW == 2 || KW == 4, "K-ways inside the workgroup");
+    constexpr int WAVES = GBN * KW;
+    constexpr int OUT_THREADS = GBN * 64;               // threads that hold the block of Y after the main loop
     constexpr int MT = BM / 16;                         // 16-row blocks of X per workgroup
-    constexpr int NT = 4 * WN;                          // 16-channel blocks per wavefront
+    constexpr int NT = 4;                               // 16-channel blocks per wavefront
     constexpr int XG = KW * BM / 8;                     // 8-row groups (1 KB of DMA each) per stage: BM / 8 per k tile
-    constexpr int XL = XG >= WAVES ? XG / WAVES : 1;    // X groups moved per wavefront and step
-    constexpr int kLoads = XL + 3 * WN + (FGQ ? 1 : 0); // DMA instructions per wavefront and step
+    constexpr int XL = (XG + WAVES - 1) / WAVES;        // X groups moved per wavefront and step
+    constexpr int PL = 3 + (FGQ ? 1 : 0);               // DMA instructions for a wavefront's planes (and scales) and step
+    constexpr int kLoads = XL + PL;
     constexpr int kXBytes = KW * BM * kTile * 2;
     constexpr int kPlaneBytes = GBN * KW * kWaveTileBytes + (FGQ ? WAVES * 256 : 0);   // per stage of the plane ring
     constexpr int kScaleOff = GBN * KW * kWaveTileBytes;          // FGQ: 256 bytes per wavefront, inside the plane stage
-    constexpr int kPlaneBase = DX * kXBytes;                      // the plane ring follows the activation ring
-    constexpr int kRingBytes = DX * kXBytes + D * kPlaneBytes;
+    constexpr int kPlaneBase = D * kXBytes;                       // the plane ring follows the activation ring
+    constexpr int kRingBytes = D * (kXBytes + kPlaneBytes);
     constexpr int kTileRegs = MT * NT * OUT_THREADS;    // float4 per output tile
-    constexpr int kSumBytes = KW > 1 ? kTileRegs * 16 : 0;        // LDS for adding the two K-ways
+    constexpr int kSumBytes = (KW - 1) * kTileRegs * 16;          // LDS for adding the K-ways
     constexpr int kSmemBytes = kRingBytes > kSumBytes ? kRingBytes : kSumBytes;
-    // loads that may still be in flight at the barrier of a step, where the next step's stage has to be there: everything
-    // issued after that stage's activations (the rest of that call's loads and DX - 2 whole calls) and after its planes
-    // (D - 2 whole calls); before the first step (kInFlight0) one call more
-    constexpr int kAfterX = 3 * WN + (FGQ ? 1 : 0);
-    constexpr int kInFlight = (DX - 2) * kLoads + kAfterX < (D - 2) * kLoads ? (DX - 2) * kLoads + kAfterX : (D - 2) * kLoads;
-    constexpr int kInFlight0 = (DX - 1) * kLoads + kAfterX < (D - 1) * kLoads ? (DX - 1) * kLoads + kAfterX : (D - 1) * kLoads;
-    // whole operands of the next step are held in registers beside this step's where they fit (see step() below)
-    constexpr bool kWhole = MT * (FGQ ? 2 : 1) <= 4;
+    // activations are read kAhead groups of MFMAs ahead, into a ring of kXRegs operands (see step() below)
+    constexpr bool kWhole = MT <= 2;                    // all of a step's operands are read a step ahead
+    constexpr int kXRegs = MT % 2 ? (MT == 3 ? 6 : MT) : 4, kAhead = kWhole ? 4 : (FGQ ? 2 : 3);
+    // the groups in which the next step's planes and activations are read for the first time
+    constexpr int kPlanesAt = MT - 1, kXAt = 2 * MT - kAhead;
+    constexpr int kPlanesEvery = (kXAt - kPlanesAt) / PL > 0 ? (kXAt - kPlanesAt) / PL : 1;
+    constexpr int kValu = layout2(FMT) ? 3 : (DQ == kIntRebias ? 8 : 2) * 8 / MT;      // vector operations behind an MFMA
+    static_assert((2 * MT) % kXRegs == 0 && kAhead < kXRegs + (kWhole ? 1 : 0), "a step starts at entry 0 of the operand ring");
     __shared__ __align__(16) unsigned char smem[kSmemBytes];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int kh = KW > 1 ? wave / NWAVES : 0;          // which of the K-ways this wavefront works on
-    const int nw = KW > 1 ? wave % NWAVES : wave;       // its position along N
+    const int kh = KW > 1 ? wave / GBN : 0;             // which of the K-ways this wavefront works on
+    const int nw = KW > 1 ? wave % GBN : wave;          // its position along N
     const int ktiles = K / kTile, nblocks = N / kTile;
     const int mblk = (M + BM - 1) / BM;
     const int nblk = (nblocks + GBN - 1) / GBN;
@@ -145,9 +144,11 @@ __global__ __launch_bounds__(GBN / WN * KW * 64, (GBN == 4 && KW == 1) ? 2 : 1) 
     const int pair = id * 8 + xcd;
     if (pair >= nblk * split_k) return;      // the grid is padded to a multiple of eight pairs
     const int nbw = pair / split_k, s = pair % split_k;
-    const int kt_begin = slice_begin(ktiles / KW, split_k, s) * KW, kt_end = slice_begin(ktiles / KW, split_k, s + 1) * KW;
+    // slices are whole steps; k tiles that fill none go to the last slice
+    const int kt_begin = slice_begin(ktiles / KW, split_k, s) * KW;
+    const int kt_end = s + 1 < split_k ? slice_begin(ktiles / KW, split_k, s + 1) * KW : ktiles;
     const int m0 = mb * BM;
-    const int nb0 = nbw * GBN + nw * WN;       // first block of output channels of this wavefront
+    const int nb0 = nbw * GBN + nw;            // block of output channels of this wavefront
     const int i = lane & 15, g = lane >> 4;
     const uint32_t smem_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
 
@@ -165,40 +166,38 @@ __global__ __launch_bounds__(GBN / WN * KW * 64, (GBN == 4 && KW == 1) ? 2 : 1) 
         xlds[p] = j * 1024;
     }
     const uint32_t wlane = lane * 16;
-    const uint32_t wlds = wave * WN * kWaveTileBytes;       // inside a stage of the plane ring
+    const uint32_t wlds = wave * kWaveTileBytes;            // inside a stage of the plane ring
     // blocks of channels past N are computed on the last valid block and dropped
-    size_t tile0[WN];
-#pragma unroll
-    for (int c = 0; c < WN; c++) tile0[c] = (size_t)min(nb0 + c, nblocks - 1) * ktiles;
+    const size_t tile0 = (size_t)min(nb0, nblocks - 1) * ktiles;
 
-    // kLoads DMA instructions per call, always: the activations of the step that starts at k tile `ktx` into stage sx
-    // of their ring, this wavefront's planes of the step that starts at `ktw` into stage sw of theirs
-    auto issue = [&](int ktx, int sx, int ktw, int sw) {
-        const uint32_t xs = smem_base + sx * kXBytes;
+    // DMA instruction p of XL: this wavefront's part of the activations of the step that starts at k tile `kt`, into stage sx
+    auto issue_x = [&](int kt, int sx, int p) {
+        const unsigned char* xb = reinterpret_cast<const unsigned char*>(X) + (size_t)kt * (kTile * 2);
+        dma16(xb, xlane[p], smem_base + sx * kXBytes + xlds[p]);
+    };
+    // DMA instruction p of PL: its own planes of the step that starts at `ktw`, into stage sw
+    auto issue_planes = [&](int ktw, int sw, int p) {
         const uint32_t sb = smem_base + kPlaneBase + sw * kPlaneBytes;
-        const unsigned char* xb = reinterpret_cast<const unsigned char*>(X) + (size_t)ktx * (kTile * 2);
-#pragma unroll
-        for (int p = 0; p < XL; p++) dma16(xb, xlane[p], xs + xlds[p]);
         const int kt = ktw + kh;          // this wavefront's k tile of the step
-#pragma unroll
-        for (int c = 0; c < WN; c++) {
-            const unsigned char* hb = reinterpret_cast<const unsigned char*>(hi) + (tile0[c] + kt) * kHiTileBytes;
-            const unsigned char* lb = reinterpret_cast<const unsigned char*>(lo) + (tile0[c] + kt) * kLoBytesOf<FMT>;
-            dma16(hb, wlane, sb + wlds + c * kWaveTileBytes);
-            dma16(hb + 1024, wlane, sb + wlds + c * kWaveTileBytes + 1024);
+        if (p < 2) {
+            const unsigned char* hb = reinterpret_cast<const unsigned char*>(hi) + (tile0 + kt) * kHiTileBytes;
+            dma16(hb + p * 1024, wlane, sb + wlds + p * 1024);
+        } else if (p == 2) {
             // FP5: the 1-bit plane has 512 bytes per tile; the upper lanes fetch them a second time
             // (into the unused half of the stage's 1 KB) rather than bytes of the next tile
-            dma16(lb, FMT != kE3M1 ? wlane : (wlane & 511u), sb + wlds + c * kWaveTileBytes + 2048);
-        }
-        if (FGQ) {
-            // scales of this tile's block for the wavefront's 64 channels: 128 bytes, fetched by lanes
+            const unsigned char* lb = reinterpret_cast<const unsigned char*>(lo) + (tile0 + kt) * kLoBytesOf<FMT>;
+            dma16(lb, FMT != kE3M1 ? wlane : (wlane & 511u), sb + wlds + 2048);
+        } else {
+            // fine-grained scales of this tile's block for the wavefront's 64 channels: 128 bytes, fetched by lanes
             // 0..31 (the upper lanes fetch the same bytes again rather than bytes past the array)
             const unsigned char* sp = reinterpret_cast<const unsigned char*>(scales) +
                                       ((size_t)(kt >> gshift) * N + (size_t)min(nb0, nblocks - 1) * kTile) * 2;
             dma4(sp, (lane & 31) * 4, sb + kScaleOff + wave * 256);
         }
     };
-    const int kt_last = kt_end - KW;      // first k tile of the last step (steps past it re-fetch it and are dropped)
+    // Steps past the end fetch the last KW k tiles again; so does the last one where the k tiles of the slice fill no whole
+    // number of steps, and a wavefront whose tile the step before has worked on gets zeros for its activations (`x_of`).
+    const int kt_last = kt_end - KW;
 
     // operand reads: row r = 16a + i, chunk 4q + g, at position (4q + g) ^ (i & 7), in this wavefront's k tile of the stage
     const int xoff0 = kh * (BM * kTile * 2) + i * (kTile * 2) + ((g ^ (i & 7)) * 16);
@@ -214,211 +213,250 @@ __global__ __launch_bounds__(GBN / WN * KW * 64, (GBN == 4 && KW == 1) ? 2 : 1) 
             if (FGQ) part[a][t] = float4v{0.f, 0.f, 0.f, 0.f};
         }
 
-    // prologue: the steps 0 .. D-1 of the planes; their activations as far as the shorter ring reaches, the step 0
-    // ones several times, and first (a call always issues kLoads loads)
+    // all of a step's, in the order in which the loop below issues them
+    auto issue = [&](int kt, int u) {
 #pragma unroll
-    for (int u = 0; u < D; u++) {
-        const int ux = u < D - DX ? 0 : u - (D - DX);
-        issue(min(kt_begin + ux * KW, kt_last), ux, min(kt_begin + u * KW, kt_last), u);
-    }
+        for (int p = 0; p < XL; p++)
+            if (kWhole) issue_x(min(kt, kt_last), u, p);
+#pragma unroll
+        for (int p = 0; p < PL; p++) issue_planes(min(kt, kt_last), u, p);
+#pragma unroll
+        for (int p = 0; p < XL; p++)
+            if (!kWhole) issue_x(min(kt, kt_last), u, p);
+    };
+
+    // prologue: the steps 0 .. D-1
+#pragma unroll
+    for (int u = 0; u < D; u++) issue(kt_begin + u * KW, u);
 
     // operand reads from a stage of the ring
-    auto read_x = [&](half8 (&x)[MT], int ux, int q) {
-        const unsigned char* st = smem + ux * kXBytes + (q ? xoff1 : xoff0);
-#pragma unroll
-        for (int a = 0; a < MT; a++) x[a] = *reinterpret_cast<const half8*>(st + a * 16 * (kTile * 2));
+    auto read_x = [&](int ux, int q, int a) {
+        return *reinterpret_cast<const half8*>(smem + ux * kXBytes + (q ? xoff1 : xoff0) + a * 16 * (kTile * 2));
     };
-    auto read_planes = [&](TileRaw (&r)[WN], int uw) {
+    auto read_planes = [&](TileRaw& r, int uw) {
         const unsigned char* wt = smem + kPlaneBase + uw * kPlaneBytes + wlds;
-#pragma unroll
-        for (int c = 0; c < WN; c++) {
-            r[c].hi0 = *reinterpret_cast<const u32x4*>(wt + c * kWaveTileBytes + wlane);
-            r[c].hi1 = *reinterpret_cast<const u32x4*>(wt + c * kWaveTileBytes + 1024 + wlane);
-            if (FMT != kE3M1) {
-                r[c].lo = *reinterpret_cast<const u32x4*>(wt + c * kWaveTileBytes + 2048 + wlane);
-            } else {
-                const u32x2 l = *reinterpret_cast<const u32x2*>(wt + c * kWaveTileBytes + 2048 + lane * 8);
-                r[c].lo = u32x4{l.x, l.y, 0u, 0u};
-            }
+        r.hi0 = *reinterpret_cast<const u32x4*>(wt + wlane);
+        r.hi1 = *reinterpret_cast<const u32x4*>(wt + 1024 + wlane);
+        if (FMT != kE3M1) {
+            r.lo = *reinterpret_cast<const u32x4*>(wt + 2048 + wlane);
+        } else {
+            const u32x2 l = *reinterpret_cast<const u32x2*>(wt + 2048 + lane * 8);
+            r.lo = u32x4{l.x, l.y, 0u, 0u};
         }
     };
-    auto read_scales = [&](half4 (&h)[4], int uw) {
-        const unsigned char* sct = smem + kPlaneBase + uw * kPlaneBytes + kScaleOff + wave * 256;
+
+    // One step (KW k tiles) is 2 * MT groups of four MFMAs: group j multiplies the 16 rows a = j % MT of X with the
+    // wavefront's 64 channels over the 32-wide k block q = j / MT.  Everything else rides between those MFMAs (which the
+    // compiler is told to keep so): in group j the operand of X for group j + kAhead is read, one MT-th of the next k block's
+    // weights is unpacked, and no two DMA instructions follow each other, which would keep the wavefront waiting.
+    // The planes are a wavefront's own: it waits for its own DMA, and refills a stage once the next one has been read.  The
+    // activations are everyone's: the barrier comes where the next step's are read first.
+    // Against reading a step's operands together behind its barrier, and unpacking each fragment in front of its MFMAs (us):
+    // 333 x 13824 x 5120 in bf16 65.1 -> 60.7, 512 x 8192 x 22016 157 -> 151, 198 random plans 4-5 % at 128 x 256, 2-3 % at
+    // 128 x 512 and 64 x 256.  At 32 rows (kWhole) a group has 29 vector operations to 4 MFMAs and nothing to hide; there
+    // all operands are read a step ahead, behind the barrier at the step's head, and each fragment is unpacked where it is used.
+    // tail < 0: a step of the steady state.  Otherwise the tail-th of the last steps, for which everything has been issued: the
+    // loads that may be in flight are those of the steps after the next, and the D-th of them has no next step.
+    TileRaw raw;                      // planes of the current step
+    u32x4 w[4];                       // unpacked weights of the current k block
+    half8 x[kXRegs];                  // activations of the next groups
+    wait_vmcnt<(D - 1) * kLoads>();
+    __syncthreads();
+    read_planes(raw, 0);
+#pragma unroll
+    for (int j = 0; j < kAhead; j++) x[j] = read_x(0, j / MT, j % MT);
+    auto read_scales = [&](half4 (&h)[4], int u) {
+        const unsigned char* sct = smem + kPlaneBase + u * kPlaneBytes + kScaleOff + wave * 256;
 #pragma unroll
         for (int t = 0; t < 4; t++) h[t] = *reinterpret_cast<const half4*>(sct + (t * 16 + g * 4) * 2);
     };
-    // the products of one 32-wide k block
-    auto mac = [&](const TileRaw (&r)[WN], const half8 (&x)[MT], int q) {
+    half4 sc4[4];                     // FGQ, kWhole: the current step's scales
+    if (kWhole) {
+        if (FGQ) read_scales(sc4, 0);
+    } else {
+        half8 h[4];
+        unpack_kblock<DQ, FMT>(raw, 0, h);
 #pragma unroll
-        for (int c = 0; c < WN; c++) {
-            half8 w4[4];
-            if (layout2(FMT)) unpack_kblock<DQ, FMT>(r[c], q, w4);     // all four fragments at once
-#pragma unroll
-            for (int t4 = 0; t4 < 4; t4++) {
-                const int t = 4 * c + t4;
-                half8 w = layout2(FMT) ? w4[t4] : unpack_tile_fragment<DQ, FMT>(r[c], 2 * t4 + q);
-#pragma unroll
-                for (int a = 0; a < MT; a++) {
-                    if (FGQ) part[a][t] = mfma16x16x32_of<FMT>(w, x[a], part[a][t]);
-                    else acc[a][t] = mfma16x16x32_of<FMT>(w, x[a], acc[a][t]);
-                }
-            }
-        }
+        for (int t = 0; t < 4; t++) w[t] = __builtin_bit_cast(u32x4, h[t]);
+    }
+    auto mac = [&](int a, int t, half8 weights, half8 activations) {
+        if (FGQ) part[a][t] = mfma16x16x32_of<FMT>(weights, activations, part[a][t]);
+        else acc[a][t] = mfma16x16x32_of<FMT>(weights, activations, acc[a][t]);
     };
 
-    // Issue order, plane layout 2 at 128 rows: an LDS read behind each of the first MFMAs (333 x 13824 x 5120 in bf16:
-    // 59.0 us, 63.0 without).  The rest is left to the compiler: that pattern costs bias-shift FP6 5 % (512 x 22016 x 8192:
-    // 170.0 us, 162.9 without), and VALU operations grouped behind every MFMA spill at 128 rows and lose 1-2 % below.
-    // The integer re-bias at 128 rows: a few vector operations behind every MFMA, or the scheduler unpacks so far ahead that six
-    // registers are spilled and reloaded inside the loop (512 x 22016 x 8192: 298 us against 340).
-    auto hints = [&](int part_of_step) {
-        if (!kWhole && DQ == kIntRebias) {
-            __builtin_amdgcn_sched_group_barrier(0x002, 50, 0);
+    // FGQ, this wavefront's last tile of a block of K (or of the workgroup's K-slice): scale and accumulate
+    auto fold = [&](int tile, bool last, const half4 (&sc)[4]) {
+        if (!FGQ) return;
+        if (((tile + KW) >> gshift) == (tile >> gshift) && !last) return;
 #pragma unroll
-            for (int n = 0; n < NT * MT; n++) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
-            }
-        }
-        if (!kWhole && layout2(FMT)) {
-            const int reads = part_of_step == 1 ? MT : 3 * WN + MT;
-#pragma unroll
-            for (int n = 0; n < reads; n++) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            }
-        }
-    };
-
-    TileRaw raw[WN];                  // planes of the current step
-    half8 x0[MT], x1[MT];             // its activations, k blocks 0 and 1 (x1 is loaded ahead only with kWhole)
-    half4 sc4[4];                     // FGQ: its scales
-    wait_vmcnt<kInFlight0>();
-    __syncthreads();
-    read_planes(raw, 0);
-    read_x(x0, 0, 0);
-    if (kWhole) read_x(x1, 0, 1);
-    if (FGQ && kWhole) read_scales(sc4, 0);
-
-    // One step (KW k tiles).  The wavefronts leave a barrier together; if they then had to read their operands from
-    // LDS, all of them would wait (88 KB at 128 rows and 128 B a cycle: 700 cycles beside 2048 of MFMAs per SIMD).  So a
-    // step starts with its operands in registers and reads the next step's behind the barrier, under its own MFMAs:
-    // with kWhole all of them; at 128 rows, where two sets don't fit the 256 registers, k block 1 is read under the
-    // MFMAs of block 0, the barrier comes between the blocks, and the next step's planes and block 0 are read under
-    // those of block 1.  Everyone's reads of the step's own stage are complete at the barrier, so that stage is refilled
-    // right behind it (planes D steps on, activations DX).  The stage numbers are compile-time constants (the loop below
-    // is unrolled over a whole period of both rings), so every LDS address is a register plus an immediate - a ring
-    // indexed at run time measured 10-20% slower.
-    // tail < 0: a step of the steady state.  Otherwise the tail-th of the last steps, for which everything has been issued: the
-    // loads that may be in flight are those of the steps after the next, and the D-th of them has no next step.  (When they
-    // over-fetched like the others, 106 x 3328 x 128 took 4.37 us against 4.18, 226 x 14208 x 1152 in FP5 15.5 against 15.0.)
-    auto step = [&](int kt, int ux, int uw, auto tail) {
-        constexpr int T = decltype(tail)::value;
-        TileRaw raw_n[WN];
-        half8 x0_n[MT], x1_n[MT];
-        half4 sc_n[4];
-        if (!kWhole) {
-            read_x(x1, ux, 1);
-            if (FGQ) read_scales(sc4, uw);
-            mac(raw, x0, 0);
-            hints(0x1);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        constexpr bool more = T < D - 1;          // the tail's last possible step has no successor
-        if constexpr (more) {
-            wait_vmcnt<(T < 0 ? kInFlight : (D - 2 - T) * kLoads)>();
-            __syncthreads();
-            if (T < 0) issue(min(kt + DX * KW, kt_last), ux, min(kt + D * KW, kt_last), uw);
-            read_planes(raw_n, (uw + 1) % D);
-            read_x(x0_n, (ux + 1) % DX, 0);
-            if (kWhole) {
-                read_x(x1_n, (ux + 1) % DX, 1);
-                if (FGQ) read_scales(sc_n, (uw + 1) % D);
-            }
-        }
-        if (kWhole) mac(raw, x0, 0);
-        mac(raw, x1, 1);
-        hints(0x2);
-        if (FGQ) {
-            // last tile of a block of K (or of this workgroup's K-slice): scale and accumulate
-            if ((((kt + 1) >> gshift) << gshift) == kt + 1 || kt + 1 == kt_end) {
-#pragma unroll
-                for (int t = 0; t < NT; t++) {
-#pragma unroll
-                    for (int a = 0; a < MT; a++) {
-#pragma unroll
-                        for (int r = 0; r < 4; r++) acc[a][t][r] += part[a][t][r] * (float)sc4[t][r];
-                        part[a][t] = float4v{0.f, 0.f, 0.f, 0.f};
-                    }
-                }
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (more) {
-#pragma unroll
-            for (int c = 0; c < WN; c++) raw[c] = raw_n[c];
+        for (int t = 0; t < NT; t++) {
 #pragma unroll
             for (int a = 0; a < MT; a++) {
-                x0[a] = x0_n[a];
-                if (kWhole) x1[a] = x1_n[a];
-            }
-            if (FGQ && kWhole) {
 #pragma unroll
-                for (int t = 0; t < 4; t++) sc4[t] = sc_n[t];
+                for (int r = 0; r < 4; r++) acc[a][t][r] += part[a][t][r] * (float)sc[t][r];
+                part[a][t] = float4v{0.f, 0.f, 0.f, 0.f};
             }
         }
     };
 
-    constexpr int P = (D % DX == 0) ? D : D * DX;      // steps after which both rings are back at stage 0
+    auto step = [&](int kt, int u, auto tail) {
+        constexpr int T = decltype(tail)::value;
+        constexpr bool more = T < D - 1;          // the tail's last possible step has no successor
+        const int tile = (T < 0 ? kt : min(kt, kt_last)) + kh;          // this wavefront's k tile
+        const uint32_t live = KW == 1 || T < 0 || tile >= kt ? ~0u : 0u;
+        auto x_of = [&](half8 v) {
+            return KW == 1 || T < 0 ? v : __builtin_bit_cast(half8, __builtin_bit_cast(u32x4, v) & live);
+        };
+        TileRaw raw_n;
+        if constexpr (kWhole) {
+            half8 xn[4];
+            half4 sc_n[4];
+            if constexpr (more) {
+                wait_vmcnt<(T < 0 ? D - 2 : D - 2 - T) * kLoads>();
+                __syncthreads();
+                if (T < 0) issue(kt + D * KW, u);
+                read_planes(raw_n, (u + 1) % D);
+#pragma unroll
+                for (int j = 0; j < 4; j++) xn[j] = read_x((u + 1) % D, j / MT, j % MT);
+                if (FGQ) read_scales(sc_n, (u + 1) % D);
+            }
+#pragma unroll
+            for (int q = 0; q < 2; q++) {
+                half8 w4[4];
+                if (layout2(FMT)) unpack_kblock<DQ, FMT>(raw, q, w4);
+#pragma unroll
+                for (int t = 0; t < 4; t++) {
+                    if (!layout2(FMT)) w4[t] = unpack_tile_fragment<DQ, FMT>(raw, 2 * t + q);
+#pragma unroll
+                    for (int a = 0; a < MT; a++) mac(a, t, w4[t], x_of(x[q * MT + a]));
+                }
+            }
+            fold(tile, kt + KW >= kt_end, sc4);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (more) {
+                raw = raw_n;
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    x[j] = xn[j];
+                    if (FGQ) sc4[j] = sc_n[j];
+                }
+            }
+            return;
+        }
+        half4 sc[4];
+        if (FGQ) read_scales(sc, u);
+#pragma unroll
+        for (int q = 0; q < 2; q++) {
+            u32x4 wn[4];
+            u32x6 merged;
+            uint32_t em, signed_em;
+#pragma unroll
+            for (int a = 0; a < MT; a++) {
+                const int j = q * MT + a, ja = j + kAhead;
+                if constexpr (more) {
+                    if (j == kPlanesAt) {
+                        wait_vmcnt<XL + (T < 0 ? D - 2 : D - 2 - T) * kLoads>();
+                        read_planes(raw_n, (u + 1) % D);
+                    }
+                    if (T < 0) {
+#pragma unroll
+                        for (int p = 0; p < PL; p++) {
+                            if (j != min(kPlanesAt + p * kPlanesEvery, kXAt)) continue;
+                            if (p == 3) asm volatile("" : "+v"(sc[0]), "+v"(sc[1]), "+v"(sc[2]), "+v"(sc[3]));    // (they have been read)
+                            issue_planes(min(kt + D * KW, kt_last), u, p);
+                        }
+                    }
+                    if (j == kXAt) {
+                        wait_vmcnt<T < 0 ? (D - 2) * kLoads + PL : (D - 2 - T) * kLoads>();
+                        __syncthreads();
+                    }
+                    if (T < 0) {
+#pragma unroll
+                        for (int p = 0; p < XL; p++)
+                            if (j == kXAt + p * kAhead / XL) issue_x(min(kt + D * KW, kt_last), u, p);
+                    }
+                }
+                if (ja < 2 * MT) x[ja % kXRegs] = read_x(u, ja / MT, ja % MT);
+                else if (more) x[ja % kXRegs] = read_x((u + 1) % D, (ja - 2 * MT) / MT, (ja - 2 * MT) % MT);
+                const half8 xa = x_of(x[j % kXRegs]);
+#pragma unroll
+                for (int t = 0; t < 4; t++) {
+                    mac(a, t, __builtin_bit_cast(half8, w[t]), xa);
+                    if (q == 0 || more) {
+                        const TileRaw& r = q ? raw_n : raw;
+                        if (layout2(FMT)) {
+                            if (a == 0 && t == 0) merged = merge_kblock(r, 1 - q);
+                            if (a == MT / 2 && t == 0) convert_kblock<FMT>(merged, wn);
+                        } else {
+                            // 32 steps over the 4 * MT MFMAs of the k block
+#pragma unroll
+                            for (int c = 0; c < 32; c++) {
+                                if (c * MT / 8 != 4 * a + t) continue;
+                                unpack_step<DQ, FMT>(r, 1 - q, c, em, signed_em, wn);
+                                // (a fragment is finished here, and not where it is used first)
+                                if ((c & 7) == 7) asm volatile("" : "+v"(wn[c >> 3]));
+                            }
+                        }
+                    }
+                }
+                // issue order of the group: each MFMA with its share of the vector operations behind it
+                if (ja < 2 * MT || more) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+#pragma unroll
+                for (int t = 0; t < 4; t++) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, kValu, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (q == 0 || more) {
+#pragma unroll
+                for (int t = 0; t < 4; t++) w[t] = wn[t];
+            }
+        }
+        fold(tile, kt + KW >= kt_end, sc);
+        if (FGQ) __builtin_amdgcn_sched_barrier(0);
+        if constexpr (more) raw = raw_n;
+    };
+
     constexpr auto steady = std::integral_constant<int, -1>();
     int kt = kt_begin;
-    if constexpr (DX == D) {
-        // steady state: branch-free trips of P steps.  One to P steps are left; their stages have all been issued by then, so
-        // they fetch nothing, and a slice of few k tiles pays for no more stages than its ring has.
-        for (; kt + P * KW < kt_end; kt += P * KW) {
+    for (; kt + D * KW < kt_end; kt += D * KW) {         // steady state: branch-free trips of D steps
 #pragma unroll
-            for (int u = 0; u < P; u++) step(kt + u * KW, u % DX, u % D, steady);
-        }
-        static_assert(P <= 4, "one line below per step");
-        auto last = [&](auto nth) {
-            constexpr int u = decltype(nth)::value;
-            if constexpr (u < P) {
-                if (kt + u * KW < kt_end) step(kt + u * KW, u % DX, u % D, nth);
-            }
-        };
-        last(std::integral_constant<int, 0>());
-        last(std::integral_constant<int, 1>());
-        last(std::integral_constant<int, 2>());
-        last(std::integral_constant<int, 3>());
-    } else {
-        for (; kt + P * KW <= kt_end; kt += P * KW) {
-#pragma unroll
-            for (int u = 0; u < P; u++) step(kt + u * KW, u % DX, u % D, steady);
-        }
-#pragma unroll
-        for (int u = 0; u < P - 1; u++) {        // the remaining steps
-            if (kt + u * KW < kt_end) step(kt + u * KW, u % DX, u % D, steady);
-        }
+        for (int u = 0; u < D; u++) step(kt + u * KW, u, steady);
     }
+    // One to D steps are left; their stages have all been issued by then, so they fetch nothing, and a slice of few k tiles
+    // pays for no more stages than its ring has.
+    static_assert(D <= 4, "one line below per step");
+    auto last = [&](auto nth) {
+        constexpr int u = decltype(nth)::value;
+        if constexpr (u < D) {
+            if (kt + u * KW < kt_end) step(kt + u * KW, u, nth);
+        }
+    };
+    last(std::integral_constant<int, 0>());
+    last(std::integral_constant<int, 1>());
+    last(std::integral_constant<int, 2>());
+    last(std::integral_constant<int, 3>());
     wait_vmcnt<0>();     // the over-fetched ring slots must land before LDS is given back
     __syncthreads();
 
-    // ---- the two K-ways of the workgroup: the second set of wavefronts hands its sums over in LDS and is done
+    // ---- the K-ways of the workgroup: all sets of wavefronts but the first hand their sums over in LDS and are done
     if (KW > 1) {
         float4v* sums = reinterpret_cast<float4v*>(smem);
-        if (kh == 1) {
+        if (kh) {
 #pragma unroll
             for (int a = 0; a < MT; a++)
 #pragma unroll
-                for (int t = 0; t < NT; t++) sums[(a * NT + t) * OUT_THREADS + nw * 64 + lane] = acc[a][t];
+                for (int t = 0; t < NT; t++) sums[((kh - 1) * MT * NT + a * NT + t) * OUT_THREADS + nw * 64 + lane] = acc[a][t];
         }
         __syncthreads();
-        if (kh == 0) {
+        if (kh) return;            // (barriers from here on wait for the wavefronts that are left)
+#pragma unroll
+        for (int k = 0; k < KW - 1; k++)
 #pragma unroll
             for (int a = 0; a < MT; a++)
 #pragma unroll
-                for (int t = 0; t < NT; t++) acc[a][t] += sums[(a * NT + t) * OUT_THREADS + nw * 64 + lane];
-        }
+                for (int t = 0; t < NT; t++) acc[a][t] += sums[(k * MT * NT + a * NT + t) * OUT_THREADS + nw * 64 + lane];
     }
 
     // Everything below is addressed through a copy of the thread index that the compiler cannot
@@ -430,29 +468,25 @@ __global__ __launch_bounds__(GBN / WN * KW * 64, (GBN == 4 && KW == 1) ? 2 : 1) 
     const int i2 = tid2 & 15, g2 = (tid2 >> 4) & 3;
 
     // ---- K-slices of other workgroups
-    const bool holds_y = KW == 1 || kh == 0;       // (wave-uniform) the wavefronts that hold the block of Y
     if (split_k > 1) {
         const int tile = nbw * mblk + mb, ntiles = mblk * nblk;
-        if (holds_y) {
-            __amdgpu_buffer_rsrc_t win = partial_window(partials + ((size_t)s * ntiles + tile) * kTileRegs, kTileRegs * 16);
-            auto store = [&](int a) {
+        __amdgpu_buffer_rsrc_t mine = partial_window(partials + ((size_t)s * ntiles + tile) * kTileRegs, kTileRegs * 16);
+        auto store = [&](int a) {
 #pragma unroll
-                for (int t = 0; t < NT; t++) store_partial(win, (a * NT + t) * OUT_THREADS + tid2, acc[a][t]);
-            };
-            if (m0 + BM <= M) {
+            for (int t = 0; t < NT; t++) store_partial(mine, tid2, acc[a][t], (a * NT + t) * OUT_THREADS);
+        };
+        if (m0 + BM <= M) {
 #pragma unroll
-                for (int a = 0; a < MT; a++) store(a);
-            } else {
+            for (int a = 0; a < MT; a++) store(a);
+        } else {
 #pragma unroll
-                for (int a = 0; a < MT; a++) {
-                    if (m0 + a * 16 >= M) break;          // rows past M: nobody reads them
-                    store(a);
-                }
+            for (int a = 0; a < MT; a++) {
+                if (m0 + a * 16 >= M) break;          // rows past M: nobody reads them
+                store(a);
             }
         }
         if (second_launch) return;                        // add_slices_kernel does the rest
         if (!arrive_last(&counters[tile * kCounterStride], (uint32_t)split_k)) return;
-        if (!holds_y) return;
         // Two slices: the one that arrives last adds the other's sums to its own, which it still holds - a + b
         // does not depend on who that is.  More slices: all of them are read back and added in slice order.
         const bool two = split_k == 2;
@@ -464,51 +498,47 @@ __global__ __launch_bounds__(GBN / WN * KW * 64, (GBN == 4 && KW == 1) ? 2 : 1) 
         }
         for (int ss = two ? 1 - s : 0; ss < (two ? 2 - s : split_k); ss++) {
             __amdgpu_buffer_rsrc_t win = partial_window(partials + ((size_t)ss * ntiles + tile) * kTileRegs, kTileRegs * 16);
-            // sixteen 16-byte loads in flight at a time: more would need registers the main loop
+            // up to AG * 4 16-byte loads in flight at a time: more would need registers the main loop
             // cannot spare
-            constexpr int AG = (MT * NT < 16) ? MT : 16 / NT;
+            constexpr int AG = MT < 4 ? MT : (MT % 4 == 0 ? 4 : (MT % 3 == 0 ? 3 : (MT == 5 ? 5 : 4)));
 #pragma unroll
             for (int a0 = 0; a0 < MT; a0 += AG) {
                 float4v v[AG][NT];
 #pragma unroll
                 for (int a = 0; a < AG; a++)
 #pragma unroll
-                    for (int t = 0; t < NT; t++) v[a][t] = load_partial(win, ((a0 + a) * NT + t) * OUT_THREADS + tid2);
+                    for (int t = 0; t < NT; t++)
+                        if (a0 + a < MT) v[a][t] = load_partial(win, tid2, ((a0 + a) * NT + t) * OUT_THREADS);
 #pragma unroll
                 for (int a = 0; a < AG; a++)
 #pragma unroll
-                    for (int t = 0; t < NT; t++) acc[a0 + a][t] += v[a][t];
+                    for (int t = 0; t < NT; t++)
+                        if (a0 + a < MT) acc[a0 + a][t] += v[a][t];
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-    } else if (!holds_y) {
-        return;
     }
 
     // ---- epilogue: lane holds channels n = 16t + 4g + r of row m = 16a + i  (i2, g2 = i, g)
+    if (nb0 >= nblocks) return;
+    float sc[4][4];
 #pragma unroll
-    for (int c = 0; c < WN; c++) {
-        const int nb = nb0 + c;
-        if (nb >= nblocks) break;
-        float sc[4][4];
+    for (int t = 0; t < 4; t++) {
+        half4 h = half4{1, 1, 1, 1};       // fine-grained scales were applied block by block
+        if (!FGQ) h = *reinterpret_cast<const half4*>(scales + (size_t)nb0 * kTile + t * 16 + g2 * 4);
 #pragma unroll
-        for (int t = 0; t < 4; t++) {
-            half4 h = half4{1, 1, 1, 1};       // fine-grained scales were applied block by block
-            if (!FGQ) h = *reinterpret_cast<const half4*>(scales + (size_t)nb * kTile + t * 16 + g2 * 4);
+        for (int r = 0; r < 4; r++) sc[t][r] = (float)h[r] * kUnshift<DQ, FMT>;
+    }
 #pragma unroll
-            for (int r = 0; r < 4; r++) sc[t][r] = (float)h[r] * kUnshift<DQ, FMT>;
-        }
+    for (int a = 0; a < MT; a++) {
+        const int m = m0 + a * 16 + i2;
+        if (m < M) {
 #pragma unroll
-        for (int a = 0; a < MT; a++) {
-            const int m = m0 + a * 16 + i2;
-            if (m < M) {
+            for (int t = 0; t < 4; t++) {
+                float yv[4];
 #pragma unroll
-                for (int t = 0; t < 4; t++) {
-                    float yv[4];
-#pragma unroll
-                    for (int r = 0; r < 4; r++) yv[r] = acc[a][c * 4 + t][r] * sc[t][r];
-                    *reinterpret_cast<half4*>(Y + (size_t)m * N + (size_t)nb * kTile + t * 16 + g2 * 4) = to_out4<FMT>(yv);
-                }
+                for (int r = 0; r < 4; r++) yv[r] = acc[a][t][r] * sc[t][r];
+                *reinterpret_cast<half4*>(Y + (size_t)m * N + (size_t)nb0 * kTile + t * 16 + g2 * 4) = to_out4<FMT>(yv);
             }
         }
     }
@@ -553,7 +583,7 @@ __global__ __launch_bounds__(256) void add_slices_kernel(const float4v* __restri
     *reinterpret_cast<half4*>(Y + (size_t)m * N + n) = to_out4<FMT>(yv);
 }
 
-template <int BM, int D, int WN, int DQ = kBiasShift, bool FGQ = false, int FMT = kE3M2, int GBN = 8, int KW = 1, int DX = D>
+template <int BM, int D, int DQ = kBiasShift, bool FGQ = false, int FMT = kE3M2, int GBN = 8, int KW = 1>
 static hipError_t launch_gemm_t(const LinearPlan& p, const uint16_t* X, int64_t M, const void* hi, const void* lo,
                                 const uint16_t* scales, int64_t N, int64_t K, uint16_t* Y, void* workspace,
                                 hipStream_t stream)
@@ -562,7 +592,7 @@ static hipError_t launch_gemm_t(const LinearPlan& p, const uint16_t* X, int64_t 
     float4v* partials = reinterpret_cast<float4v*>(reinterpret_cast<char*>(workspace) + kZeroBytes);
     const int64_t mblk = (M + BM - 1) / BM, nblk = (N / kTile + GBN - 1) / GBN;
     const unsigned grid = (unsigned)(mblk * ((nblk * p.split_k + 7) / 8 * 8));   // padded: see the id mapping
-    hipLaunchKernelGGL((gemm_kernel<BM, D, WN, DQ, FGQ, FMT, GBN, KW, DX>), dim3(grid), dim3(GBN / WN * KW * 64), 0, stream, X, (int)M,
+    hipLaunchKernelGGL((gemm_kernel<BM, D, DQ, FGQ, FMT, GBN, KW>), dim3(grid), dim3(GBN * KW * 64), 0, stream, X, (int)M,
                        (const u32x4*)hi, (const u32x4*)lo, scales, (int)N, (int)K, Y, partials, counters, p.split_k, p.gshift, p.second_launch);
     if (p.second_launch) {
         const hipError_t e = hipGetLastError();

@@ -24,15 +24,16 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t partial_window(float4v* base, 
     return __builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00020000);
 }
 
-__device__ __forceinline__ void store_partial(__amdgpu_buffer_rsrc_t win, uint32_t index, float4v v)
+// Element `index + first`; `first` is the same for all lanes and travels in a scalar register.
+__device__ __forceinline__ void store_partial(__amdgpu_buffer_rsrc_t win, uint32_t index, float4v v, uint32_t first = 0)
 {
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), win, index * 16u, 0, kAgentCoherent);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), win, index * 16u, first * 16u, kAgentCoherent);
 }
 
 // Only meaningful after arrive_last() returned true.
-__device__ __forceinline__ float4v load_partial(__amdgpu_buffer_rsrc_t win, uint32_t index)
+__device__ __forceinline__ float4v load_partial(__amdgpu_buffer_rsrc_t win, uint32_t index, uint32_t first = 0)
 {
-    return __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(win, index * 16u, 0, kAgentCoherent));
+    return __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(win, index * 16u, first * 16u, kAgentCoherent));
 }
 
 // Must be called by every thread of the workgroup (it contains barriers).
