@@ -274,7 +274,8 @@ typedef struct fp6_plan_info {
     int variant;            /* FP6_VARIANT_DECODE or FP6_VARIANT_GEMM                                   */
     int split_k;            /* K-slices handled by separate workgroups (1 = K is not split); slices of an
                                automatic plan may differ by a k tile or two, forced ones may not      */
-    int block_m;            /* rows of X per workgroup: gemm 32/64/128; decode 16, 32 or 64             */
+    int block_m;            /* rows of X per workgroup: gemm 32 to 128, a multiple of 16 (64 and 128 are cut to
+                               what M needs, forced heights are not); decode 16, 32 or 64              */
     int width;              /* 64-channel blocks per workgroup: gemm 8 or 4; decode 1                   */
     int waves;              /* wavefronts per workgroup                                                */
     int depth;              /* tiles (decode) or stages (gemm) in the prefetch ring                    */

@@ -7,6 +7,7 @@ hipError_t launch_gemm(const LinearPlan& p, const uint16_t* X, int64_t M, const 
                        const uint16_t* scales, int64_t N, int64_t K, uint16_t* Y, void* workspace,
                        hipStream_t stream)
 {
+    if (p.block_m & (p.block_m - 1)) return launch_gemm_heights(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
     if (p.format != kE3M2 || p.gshift >= 0 || p.dequant != kBiasShift)
         return launch_gemm_variant(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
     // Four-wavefront workgroups are built so that two fit a compute unit (at most 256 registers per lane and

@@ -1,8 +1,8 @@
 // Tiled kernel (any M) of the W6A16 linear layer for gfx950: the kernel template and its launcher.
 // Included by the translation units that instantiate it (fp6_gemm.hip: the FP6 bias-shift kernels;
-// fp6_gemm_variants.hip: ablations, fine-grained scales, FP5).
+// fp6_gemm_variants.hip: ablations, fine-grained scales, FP5; fp6_gemm_heights*.hip: heights between the powers of two).
 //
-// A workgroup computes a BM x (64 * GBN) block of Y, GBN = 8 or 4.  Its wavefronts stand side by
+// A workgroup computes a BM x (64 * GBN) block of Y, BM = 32 to 128 in steps of 16, GBN = 8 or 4.  Its wavefronts stand side by
 // side along N, one per 64 output channels (two per SIMD at GBN = 8).  Every packed
 // weight is fetched and padded to fp16 (bias shift, Section 5.2) by exactly one
 // wavefront and goes straight into MFMA operand registers - the dequantized weight never
@@ -120,7 +120,7 @@ __global__ __launch_bounds__(GBN * KW * 64, (GBN == 4 && KW == 1 && BM <= 128) ?
     // the groups in which the next step's planes and activations are read for the first time
     constexpr int kPlanesAt = MT - 1, kXAt = 2 * MT - kAhead;
     constexpr int kPlanesEvery = (kXAt - kPlanesAt) / PL > 0 ? (kXAt - kPlanesAt) / PL : 1;
-    constexpr int kValu = layout2(FMT) ? 3 : (DQ == kIntRebias ? 8 : 2) * 8 / MT;      // vector operations behind an MFMA
+    constexpr int kValu = layout2(FMT) ? 3 : ((DQ == kIntRebias ? 8 : 2) * 8 + MT - 1) / MT;      // vector operations behind an MFMA
     static_assert((2 * MT) % kXRegs == 0 && kAhead < kXRegs + (kWhole ? 1 : 0), "a step starts at entry 0 of the operand ring");
     __shared__ __align__(16) unsigned char smem[kSmemBytes];
 

@@ -39,7 +39,7 @@ hipError_t launch_dequantize(int format, const void* hi, const void* lo, const u
 struct LinearPlan {
     int variant;        // FP6_VARIANT_DECODE or FP6_VARIANT_GEMM
     int split_k;        // K-slices handled by separate workgroups (>= 1)
-    int block_m;        // GEMM: rows of X per workgroup (32, 64 or 128); DECODE: 16
+    int block_m;        // GEMM: rows of X per workgroup (32, 48, 64, 80, 96, 112 or 128); DECODE: 16
     int waves;          // wavefronts per workgroup
     int depth;          // tiles in the per-wavefront prefetch ring
     size_t partial_bytes;   // fp32 partial sums needed in the workspace (0 if split_k == 1)
@@ -51,7 +51,7 @@ struct LinearPlan {
     int half_tiles;     // DECODE: workgroups own 32 channels (half a tile) instead of 64
     int pairwise;       // DECODE with split_k > 1: K-slices meet pairwise in the slot region (1) or at a counter (0)
     int second_launch;  // GEMM with split_k > 1: the slices are added by a second kernel (1) or by the last workgroup to arrive (0)
-    int kw;             // GEMM: K-ways inside the workgroup (1, or 2 with gbn = 4 and block_m = 128)
+    int kw;             // GEMM: K-ways inside the workgroup (1, or 2 with gbn = 4 and block_m of 80 and more)
 };
 
 // Heuristic (or caller-forced) plan; returns false if the request is invalid for the shape.
@@ -81,6 +81,13 @@ hipError_t launch_gemm_variant(const LinearPlan& p, const uint16_t* X, int64_t M
 hipError_t launch_gemm_bf16(const LinearPlan& p, const uint16_t* X, int64_t M, const void* hi, const void* lo,
                                const uint16_t* scales, int64_t N, int64_t K, uint16_t* Y, void* workspace,
                                hipStream_t stream);
+// fp6_gemm_heights*.hip: plans with 48, 80, 96 or 112 rows per workgroup
+hipError_t launch_gemm_heights(const LinearPlan& p, const uint16_t* X, int64_t M, const void* hi, const void* lo,
+                               const uint16_t* scales, int64_t N, int64_t K, uint16_t* Y, void* workspace, hipStream_t stream);
+hipError_t launch_gemm_heights_v2(const LinearPlan& p, const uint16_t* X, int64_t M, const void* hi, const void* lo,
+                               const uint16_t* scales, int64_t N, int64_t K, uint16_t* Y, void* workspace, hipStream_t stream);
+hipError_t launch_gemm_heights_fp5_fgq(const LinearPlan& p, const uint16_t* X, int64_t M, const void* hi, const void* lo,
+                               const uint16_t* scales, int64_t N, int64_t K, uint16_t* Y, void* workspace, hipStream_t stream);
 hipError_t launch_gemm(const LinearPlan& p, const uint16_t* X, int64_t M, const void* hi, const void* lo,
                        const uint16_t* scales, int64_t N, int64_t K, uint16_t* Y, void* workspace,
                        hipStream_t stream);
