@@ -17,6 +17,8 @@
 #include "fp6_internal.hpp"
 #include "fp6_reduce.hpp"
 
+#include <type_traits>
+
 namespace fp6 {
 
 struct XFrag {
@@ -32,6 +34,53 @@ __device__ __forceinline__ XFrag load_x(const uint16_t* __restrict__ xrow, int k
     x.q0 = p[0];
     x.q1 = p[4];   // +32 halfs
     return x;
+}
+
+// The same tile of X by whole lines: an operand slice belongs to a row, so sixteen neighbouring lanes of load_x ask for sixteen
+// lines, where here eight lanes share one.  (With one block of 16 rows no faster, and 5 % slower on short streams.)  The piece of
+// row 8p + lane / 8 that a lane holds goes to the operand layout through the wavefront's own 2 KB of LDS (16-byte chunk c of row r
+// at chunk position c ^ (r & 7): no bank conflicts either way).
+__device__ __forceinline__ XFrag load_x_lines(const uint16_t* const (&xline)[2], int kt)
+{
+    XFrag x;
+    x.q0 = *reinterpret_cast<const half8*>(xline[0] + (size_t)kt * kTile);
+    x.q1 = *reinterpret_cast<const half8*>(xline[1] + (size_t)kt * kTile);
+    return x;
+}
+
+template <int MB>
+__device__ __forceinline__ void turn_x(const XFrag (&lines)[MB], unsigned char* own, int lane, XFrag (&x)[MB])
+{
+    const int m = lane & 15, g = lane >> 4;
+    // (DS instructions of a wavefront are carried out in order: no wait between the two, or against the tile before)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int c = 0; c < MB; c++) {
+        unsigned char* p = own + c * 2048 + (lane >> 3) * 128 + ((lane & 7) ^ (lane >> 3)) * 16;
+        *reinterpret_cast<half8*>(p) = lines[c].q0;
+        *reinterpret_cast<half8*>(p + 1024) = lines[c].q1;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int c = 0; c < MB; c++) {
+        const unsigned char* p = own + c * 2048 + m * 128;
+        x[c].q0 = *reinterpret_cast<const half8*>(p + (g ^ (m & 7)) * 16);
+        x[c].q1 = *reinterpret_cast<const half8*>(p + ((4 + g) ^ (m & 7)) * 16);
+    }
+}
+
+// f(integral_constant<n>) for a wavefront-uniform n of 1 .. Max (nothing for 0): the last tiles of a wavefront run as straight code
+// for their number, with exact waits.  Behind a branch around each of them the compiler has to wait for the fewest loads that may
+// be in flight.  (Tried beside it, slower: null loads past the end, in one loop; a branch at every step of the ring's phase.)
+template <int Max, class F>
+__device__ __forceinline__ void with_count(int n, F f)
+{
+    if constexpr (Max > 0) {
+        if (n == Max) f(std::integral_constant<int, Max>());
+        else with_count<Max - 1>(n, f);
+    }
 }
 
 // One tile against MB blocks of 16 rows of X: every fragment is unpacked once and used MB times.
@@ -60,7 +109,10 @@ __device__ __forceinline__ void tile_mac(const TileRaw& r, const XFrag (&x)[MB],
 }
 
 // D = depth of the per-wavefront ring of tiles in flight (D-1 tiles are being fetched
-// while one is consumed).  The ring is indexed with compile-time constants only.
+// while one is consumed).  The ring is indexed with compile-time constants only.  A wavefront's tiles are addressed from scalar
+// registers; with that and the barriers to scheduling in the stream, plane layout 2 takes 0.90 of the time at up to 16 rows, the rest 0.99.
+// EXACT: the last tiles run as straight code, and several blocks of rows of X are fetched by whole lines (see runs_exact and load_x_lines):
+// 0.92 of the time where a launch takes it; 8 x 5120 x 13824 with a scale to 128 elements 14.0 -> 13.2 us, 32 x 13824 x 5120 16.8 -> 15.1.
 // FGQ: one scale per `64 << gshift` elements along K (Section 3, fine-grained quantization)
 // instead of one per row.  A tile lies inside one such block, so its product sums are
 // formed in a zeroed accumulator and multiplied by the block's scales while they are added
@@ -73,14 +125,15 @@ __device__ __forceinline__ void tile_mac(const TileRaw& r, const XFrag (&x)[MB],
 // nb = the workgroup's block of 64 output channels, s = its K-slice.  gnb = the index under which the block meets
 // its other K-slices in the workspace: nb for a single layer; in a group of layers launched together, the block's
 // index in the concatenation of their channel blocks.
-template <int WAVES, int D, int DQ, bool FGQ, int FMT, int MB>
+template <int WAVES, int D, int DQ, bool FGQ, int FMT, int MB, bool EXACT>
 __device__ __forceinline__ void decode_block(
     const uint16_t* __restrict__ X, int M, const u32x4* __restrict__ hi, const u32x4* __restrict__ lo,
     const uint16_t* __restrict__ scales, int N, int K, uint16_t* __restrict__ Y,
     float4v* __restrict__ partials, uint32_t* __restrict__ counters, unsigned long long* __restrict__ slots,
     int split_k, int pairwise, int gshift, int nb, int s, int gnb)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    constexpr bool LINES = EXACT && MB > 1;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ktiles = K / kTile;
     const int kt_begin = slice_begin(ktiles, split_k, s), kt_end = slice_begin(ktiles, split_k, s + 1);
     static_assert(MB == 1 || !FGQ, "several row blocks: row-wise scales only");
@@ -88,6 +141,11 @@ __device__ __forceinline__ void decode_block(
     const uint16_t* xrow[MB];
 #pragma unroll
     for (int c = 0; c < MB; c++) xrow[c] = X + (size_t)min(16 * c + m, M - 1) * K + g * 8;
+    const uint16_t* xline[MB][2];
+#pragma unroll
+    for (int c = 0; c < MB; c++)
+#pragma unroll
+        for (int p = 0; p < 2; p++) xline[c][p] = X + (size_t)min(16 * c + 8 * p + (lane >> 3), M - 1) * K + (lane & 7) * 8;
     const size_t tile0 = (size_t)nb * ktiles;
 
     // row scales of the four channels this thread will store (fetched early: the epilogue is latency-bound)
@@ -126,18 +184,19 @@ __device__ __forceinline__ void decode_block(
     const int cnt = (kt_end - kt0 + WAVES - 1) / WAVES;
     if (cnt > 0) {
         TileRaw raw[D];
+        auto tile_at = [&](int j) { return kt0 + j * WAVES; };
         XFrag xf[D][MB];
         auto fetch_x = [&](int slot, int k) {
 #pragma unroll
-            for (int c = 0; c < MB; c++) xf[slot][c] = load_x(xrow[c], k);
+            for (int c = 0; c < MB; c++) xf[slot][c] = LINES ? load_x_lines(xline[c], k) : load_x(xrow[c], k);
         };
         // k = the tile's index along K
-        auto mac = [&](int slot, int k) {
+        auto mac = [&](int slot, const XFrag (&x)[MB], int k) {
             if (FGQ) {
                 float4v part[MB][4];
 #pragma unroll
                 for (int t = 0; t < 4; t++) part[0][t] = float4v{0.f, 0.f, 0.f, 0.f};
-                tile_mac<DQ, FMT, MB>(raw[slot], xf[slot], part);
+                tile_mac<DQ, FMT, MB>(raw[slot], x, part);
                 const uint16_t* sg = gscale + ((k >> gshift) - group0) * kTile + g * 4;
 #pragma unroll
                 for (int t = 0; t < 4; t++) {
@@ -146,40 +205,103 @@ __device__ __forceinline__ void decode_block(
                     for (int r = 0; r < 4; r++) acc[0][t][r] += part[0][t][r] * (float)sv[r];
                 }
             } else {
-                tile_mac<DQ, FMT, MB>(raw[slot], xf[slot], acc);
+                tile_mac<DQ, FMT, MB>(raw[slot], x, acc);
             }
         };
 
-        // prologue: tiles 0 .. D-2 (clamped: a short wavefront re-reads its last tile)
+        if constexpr (!LINES) {
+            // prologue: tiles 0 .. D-2 (clamped: a short wavefront re-reads its last tile)
 #pragma unroll
-        for (int u = 0; u < D - 1; u++) {
-            const int k = kt0 + min(u, cnt - 1) * WAVES;
-            raw[u] = load_tile<FMT>(hi, lo, tile0 + k, lane);
-            fetch_x(u, k);
-        }
-        // steady state, branch-free: D tiles per trip, each step refills the slot freed one step ago
-        int j0 = 0;
-        for (; j0 + 2 * D - 1 <= cnt; j0 += D) {
-#pragma unroll
-            for (int u = 0; u < D; u++) {
-                const int k = kt0 + (j0 + u + D - 1) * WAVES;
-                raw[(u + D - 1) % D] = load_tile<FMT>(hi, lo, tile0 + k, lane);
-                fetch_x((u + D - 1) % D, k);
-                mac(u, kt0 + (j0 + u) * WAVES);
+            for (int u = 0; u < D - 1; u++) {
+                const int k = tile_at(min(u, cnt - 1));
+                raw[u] = load_tile<FMT>(hi, lo, tile0 + k, lane);
+                fetch_x(u, k);
             }
-        }
-        // drain: the remaining (< 2D-1) tiles, refilling only while tiles are left
+            // steady state, branch-free: D tiles per trip, each step refills the slot freed one step ago
+            int j0 = 0;
+            for (; j0 + 2 * D - 1 <= cnt; j0 += D) {
 #pragma unroll
-        for (int v = 0; v < 2 * D - 2; v++) {
-            const int j = j0 + v;
-            if (j < cnt) {
-                if (j + D - 1 < cnt) {
-                    const int k = kt0 + (j + D - 1) * WAVES;
-                    raw[(v + D - 1) % D] = load_tile<FMT>(hi, lo, tile0 + k, lane);
-                    fetch_x((v + D - 1) % D, k);
+                for (int u = 0; u < D; u++) {
+                    const int k = tile_at(j0 + u + D - 1);
+                    raw[(u + D - 1) % D] = load_tile<FMT>(hi, lo, tile0 + k, lane);
+                    fetch_x((u + D - 1) % D, k);
+                    __builtin_amdgcn_sched_barrier(0);          // (left alone, the compiler sinks the loads towards their use)
+                    mac(u, xf[u], tile_at(j0 + u));
+                    if (!EXACT) __builtin_amdgcn_sched_barrier(0);
                 }
-                mac(v % D, kt0 + j * WAVES);
             }
+            if constexpr (!EXACT) {
+                // the remaining (< 2D-1) tiles, refilling only while tiles are left
+#pragma unroll
+                for (int v = 0; v < 2 * D - 2; v++) {
+                    const int j = j0 + v;
+                    if (j < cnt) {
+                        if (j + D - 1 < cnt) {
+                            const int k = tile_at(j + D - 1);
+                            raw[(v + D - 1) % D] = load_tile<FMT>(hi, lo, tile0 + k, lane);
+                            fetch_x((v + D - 1) % D, k);
+                        }
+                        mac(v % D, xf[v % D], tile_at(j));
+                    }
+                }
+            } else {
+                // the same as straight code for the number of tiles left
+                with_count<2 * D - 2>(cnt - j0, [&](auto left) {
+#pragma unroll
+                    for (int v = 0; v < left(); v++) {
+                        if (v + D - 1 < left()) {
+                            const int k = tile_at(j0 + v + D - 1);
+                            raw[(v + D - 1) % D] = load_tile<FMT>(hi, lo, tile0 + k, lane);
+                            fetch_x((v + D - 1) % D, k);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                        mac(v % D, xf[v % D], tile_at(j0 + v));
+                    }
+                });
+            }
+        } else {
+            // X is fetched one tile further ahead than the planes and turned one tile ahead of its use: by then the wavefront
+            // waits for the planes of the same age, and the turn's trip through LDS is hidden behind a tile's work.
+            __shared__ __align__(16) unsigned char xturn[WAVES * MB * 2048];
+            unsigned char* own = xturn + wave * MB * 2048;
+            XFrag x[MB], xn[MB];
+            auto refill = [&](int slot_w, int jw, int slot_x, int jx) {
+                raw[slot_w] = load_tile<FMT>(hi, lo, tile0 + tile_at(jw), lane);
+                fetch_x(slot_x, tile_at(jx));
+            };
+            auto turn_and_mac = [&](int slot, int j) {
+                turn_x<MB>(xf[(slot + 1) % D], own, lane, xn);
+                __builtin_amdgcn_sched_barrier(0);
+                mac(slot, x, tile_at(j));
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int c = 0; c < MB; c++) x[c] = xn[c];
+            };
+            fetch_x(0, tile_at(0));
+#pragma unroll
+            for (int u = 0; u < D - 1; u++) refill(u, min(u, cnt - 1), u + 1, min(u + 1, cnt - 1));
+            turn_x<MB>(xf[0], own, lane, x);
+            int j0 = 0;
+            for (; j0 + 2 * D <= cnt; j0 += D) {
+#pragma unroll
+                for (int u = 0; u < D; u++) {
+                    refill((u + D - 1) % D, j0 + u + D - 1, u, j0 + u + D);
+                    turn_and_mac(u, j0 + u);
+                }
+            }
+            with_count<2 * D - 1>(cnt - j0, [&](auto left) {
+#pragma unroll
+                for (int v = 0; v < left(); v++) {
+                    if (v + D - 1 < left()) raw[(v + D - 1) % D] = load_tile<FMT>(hi, lo, tile0 + tile_at(j0 + v + D - 1), lane);
+                    if (v + D < left()) fetch_x(v % D, tile_at(j0 + v + D));
+                    if (v + 1 < left()) turn_x<MB>(xf[(v + 1) % D], own, lane, xn);
+                    __builtin_amdgcn_sched_barrier(0);
+                    mac(v % D, x, tile_at(j0 + v));
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int c = 0; c < MB; c++) x[c] = xn[c];
+                }
+            });
         }
     }
 
@@ -268,15 +390,15 @@ __device__ __forceinline__ void decode_block(
     }
 }
 
-template <int WAVES, int D, int DQ, bool FGQ, int FMT, int MB>
-__global__ __launch_bounds__(WAVES * 64) void decode_kernel(
+template <int WAVES, int D, int DQ, bool FGQ, int FMT, int MB, bool EXACT>
+__global__ __launch_bounds__(WAVES * 64, WAVES != 4 || MB > 1 || EXACT ? 1 : FGQ || layout2(FMT) ? 3 : 4) void decode_kernel(
     const uint16_t* __restrict__ X, int M, const u32x4* __restrict__ hi, const u32x4* __restrict__ lo,
     const uint16_t* __restrict__ scales, int N, int K, uint16_t* __restrict__ Y,
     float4v* __restrict__ partials, uint32_t* __restrict__ counters, unsigned long long* __restrict__ slots,
     int split_k, int pairwise, int gshift)
 {
     const int nb = blockIdx.x / split_k, s = blockIdx.x % split_k;
-    decode_block<WAVES, D, DQ, FGQ, FMT, MB>(X, M, hi, lo, scales, N, K, Y, partials, counters, slots, split_k, pairwise,
+    decode_block<WAVES, D, DQ, FGQ, FMT, MB, EXACT>(X, M, hi, lo, scales, N, K, Y, partials, counters, slots, split_k, pairwise,
                                              gshift, nb, s, nb);
 }
 
@@ -316,15 +438,15 @@ __device__ __forceinline__ DecodeLayer layer_of(const DecodeGroup& g, int gnb, i
     return a;
 }
 
-template <int WAVES, int D>
-__global__ __launch_bounds__(WAVES * 64) void decode_group_kernel(
+template <int WAVES, int D, bool EXACT>
+__global__ __launch_bounds__(WAVES * 64, EXACT ? 1 : 4) void decode_group_kernel(
     DecodeGroup g, int M, int K, float4v* __restrict__ partials, uint32_t* __restrict__ counters,
     unsigned long long* __restrict__ slots, int split_k, int pairwise)
 {
     const int gnb = __builtin_amdgcn_readfirstlane(blockIdx.x / split_k), s = blockIdx.x % split_k;
     int first;
     const DecodeLayer a = layer_of(g, gnb, &first);
-    decode_block<WAVES, D, kBiasShift, false, kE3M2, 1>(a.X, M, a.hi, a.lo, a.scales, a.N, K, a.Y, partials, counters,
+    decode_block<WAVES, D, kBiasShift, false, kE3M2, 1, EXACT>(a.X, M, a.hi, a.lo, a.scales, a.N, K, a.Y, partials, counters,
                                                         slots, split_k, pairwise, -1, gnb - first, s, gnb);
 }
 
@@ -363,7 +485,7 @@ __device__ __forceinline__ void decode_half_block(
     float4v* __restrict__ partials, uint32_t* __restrict__ counters, unsigned long long* __restrict__ slots,
     int split_k, int pairwise, int h, int nb, int s, int gnb)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ktiles = K / kTile;
     const int kt_begin = slice_begin(ktiles, split_k, s), kt_end = slice_begin(ktiles, split_k, s + 1);
     const int m = lane & 15, g = lane >> 4;
@@ -403,21 +525,22 @@ __device__ __forceinline__ void decode_half_block(
                 const int k = kt0 + (j0 + u + D - 1) * WAVES;
                 raw[(u + D - 1) % D] = load_half<FMT>(hi, lo, tile0 + k, lane, h);
                 xf[(u + D - 1) % D] = load_x(xrow, k);
+                __builtin_amdgcn_sched_barrier(0);
                 mac(raw[u], xf[u]);
             }
         }
+        with_count<2 * D - 2>(cnt - j0, [&](auto left) {
 #pragma unroll
-        for (int v = 0; v < 2 * D - 2; v++) {
-            const int j = j0 + v;
-            if (j < cnt) {
-                if (j + D - 1 < cnt) {
-                    const int k = kt0 + (j + D - 1) * WAVES;
+            for (int v = 0; v < left(); v++) {
+                if (v + D - 1 < left()) {
+                    const int k = kt0 + (j0 + v + D - 1) * WAVES;
                     raw[(v + D - 1) % D] = load_half<FMT>(hi, lo, tile0 + k, lane, h);
                     xf[(v + D - 1) % D] = load_x(xrow, k);
                 }
+                __builtin_amdgcn_sched_barrier(0);
                 mac(raw[v % D], xf[v % D]);
             }
-        }
+        });
     }
 
     // thread m*8 + (4t + g) takes channels 16t + 4g + r of column m  (t = 0, 1)
@@ -525,6 +648,17 @@ static hipError_t launch_decode_half_t(const LinearPlan& p, const uint16_t* X, i
     return hipGetLastError();
 }
 
+// Which of the two forms of decode_block a launch takes.  Straight code for the last tiles needs registers (172 to 208 of a lane's
+// 512, 340 and 512 with several row blocks; the short form 104 to 136, 184 and 264): it is for launches whose workgroups then still
+// fit the chip at once, two to a compute unit or one.  With three tiles or less to a wavefront there is nothing but last tiles, and the code
+// of their number is fetched for one use.  Measured against one form for all, time by tiles to a wavefront: 2 1.04, 2 to 3 1.00, 3 to 4 0.95,
+// 4 to 6 0.90, above 0.94 (363 random layers of 1 to 16 rows, all formats); with 17 to 64 rows 1.03, 0.99, 0.98, 0.98 and 0.95 (46 layers);
+// 618 and 648 workgroups of it 1.15 and 1.21.
+static bool runs_exact(int64_t K, int split_k, int64_t workgroups, int mb)
+{
+    return workgroups <= (mb == 1 ? 512 : 256) && (K / kTile + split_k - 1) / split_k > 3 * 4;
+}
+
 template <int WAVES, int D, int DQ = kBiasShift, bool FGQ = false, int FMT = kE3M2, int MB = 1>
 static hipError_t launch_decode_t(const LinearPlan& p, const uint16_t* X, int64_t M, const void* hi, const void* lo,
                                   const uint16_t* scales, int64_t N, int64_t K, uint16_t* Y, void* workspace,
@@ -536,9 +670,17 @@ static hipError_t launch_decode_t(const LinearPlan& p, const uint16_t* X, int64_
     const unsigned grid = (unsigned)((N / kTile) * p.split_k);
     // FGQ: 128 bytes of scales per block of K in a workgroup's slice (a slice may start inside a block)
     const size_t lds = FGQ ? (size_t)((((K / kTile + p.split_k - 1) / p.split_k - 1) >> p.gshift) + 2) * 128 : 0;
-    hipLaunchKernelGGL((decode_kernel<WAVES, D, DQ, FGQ, FMT, MB>), dim3(grid), dim3(WAVES * 64), lds, stream, X, (int)M,
-                       (const u32x4*)hi, (const u32x4*)lo, scales, (int)N, (int)K, Y, partials, counters, slots,
-                       p.split_k, p.pairwise, p.gshift);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(WAVES * 64), lds, stream, X, (int)M, (const u32x4*)hi, (const u32x4*)lo, scales,
+                           (int)N, (int)K, Y, partials, counters, slots, p.split_k, p.pairwise, p.gshift);
+    };
+    if constexpr (WAVES == 4 && DQ == kBiasShift && D == (MB == 4 ? 3 : 4)) {
+        if (runs_exact(K, p.split_k, grid, MB)) {
+            launch(decode_kernel<WAVES, D, DQ, FGQ, FMT, MB, true>);
+            return hipGetLastError();
+        }
+    }
+    launch(decode_kernel<WAVES, D, DQ, FGQ, FMT, MB, false>);
     return hipGetLastError();
 }
 
@@ -591,8 +733,12 @@ hipError_t launch_decode_group(const LinearPlan& p, int count, const GroupLayer*
         hipLaunchKernelGGL((decode_half_group_kernel<4, 4>), dim3(grid), dim3(256), 0, stream, g, (int)M, (int)K, (int)units,
                            partials, counters, slots, p.split_k, p.pairwise);
     } else {
-        hipLaunchKernelGGL((decode_group_kernel<4, 4>), dim3((unsigned)units), dim3(256), 0, stream, g, (int)M, (int)K,
-                           partials, counters, slots, p.split_k, p.pairwise);
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)units), dim3(256), 0, stream, g, (int)M, (int)K, partials, counters, slots, p.split_k,
+                               p.pairwise);
+        };
+        if (runs_exact(K, p.split_k, units, 1)) launch(decode_group_kernel<4, 4, true>);
+        else launch(decode_group_kernel<4, 4, false>);
     }
     return hipGetLastError();
 }
