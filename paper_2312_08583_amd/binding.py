@@ -1,4 +1,4 @@
-"""Thin ctypes binding of libfp6_linear.so (the C ABI in include/fp6_linear.h).
+"""Thin binding of libfp6_linear.so (the C ABI in include/fp6_linear.h): ctypes, and native marshalling for the hot-path calls.
 
 Argument marshalling only: every step of the path runs in the HIP kernels.  PyTorch is
 used for device memory and for the current stream, nothing else.  There is no CPU
@@ -83,6 +83,27 @@ class PlanInfo(ctypes.Structure):
 _LIB = None
 
 
+def _not_loaded(*_):
+    return None
+
+
+# Marshalling in native code (csrc/fp6_python.cpp): the result of a plain call with its workspace, or None, and then the routines below
+# take the call: the checks are the same, allocations and errors are theirs.
+_native_linear = _native_group = _not_loaded
+_LINEAR, _VARIANT, _FGQ, _FP5, _V2, _V2_BF16 = range(6)
+
+
+def _bind_native(L: ctypes.CDLL) -> None:
+    global _native_linear, _native_group
+    from . import _native
+    entries = (L.fp6_linear, L.fp6_linear_variant, L.fp6_linear_fgq, L.fp5_linear, L.fp6_linear_v2, L.fp6_linear_v2_bf16,
+               L.fp6_linear_group, L.fp6_linear_workspace_bytes, L.fp6_linear_variant_workspace_bytes,
+               L.fp6_linear_fgq_workspace_bytes, L.fp5_linear_workspace_bytes, L.fp6_linear_v2_workspace_bytes,
+               L.fp6_linear_group_workspace_bytes)
+    _native.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in entries), _check)
+    _native_linear, _native_group = _native.linear, _native.group
+
+
 class Fp6Error(RuntimeError):
     pass
 
@@ -92,9 +113,11 @@ def lib() -> ctypes.CDLL:
     global _LIB
     if _LIB is not None:
         return _LIB
+    from . import build as _build
     if not os.path.exists(LIB_PATH):
-        from . import build as _build
         _build.build()
+    if not os.path.exists(_build.NATIVE):
+        _build.build_native()
     L = ctypes.CDLL(LIB_PATH)
     i64, p, sz, ci = ctypes.c_int64, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int
     L.fp6_layout_version.restype = ci
@@ -161,6 +184,7 @@ def lib() -> ctypes.CDLL:
     L.fp6_linear_group.argtypes = [i64, ctypes.POINTER(LinearProblem), ci, p, sz, p]
     L.fp6_linear_plan.restype = ci
     L.fp6_linear_plan.argtypes = [ci, i64, i64, i64, i64, ci, ci, ctypes.POINTER(PlanInfo)]
+    _bind_native(L)
     _LIB = L
     return L
 
@@ -338,6 +362,9 @@ def fp6_linear_variant_workspace_bytes(M: int, N: int, K: int, variant: int, spl
 def fp6_linear_variant(X: torch.Tensor, hi: torch.Tensor, lo: torch.Tensor, scales: torch.Tensor, N: int, K: int,
                        variant: int = FP6_VARIANT_AUTO, split_k: int = 0, out: Optional[torch.Tensor] = None,
                        workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
+    Y = _native_linear(_VARIANT, X, hi, lo, scales, N, K, 0, out, workspace, variant, split_k)
+    if Y is not None:
+        return Y
     need = lambda M: fp6_linear_variant_workspace_bytes(M, N, K, variant, split_k)
     return _linear("fp6_linear_variant", need, X, hi, lo, scales, N, K, out, workspace, (variant, split_k))
 
@@ -345,6 +372,9 @@ def fp6_linear_variant(X: torch.Tensor, hi: torch.Tensor, lo: torch.Tensor, scal
 def fp6_linear(X: torch.Tensor, hi: torch.Tensor, lo: torch.Tensor, scales: torch.Tensor, N: int, K: int,
                out: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Y[M,N] = X[M,K] x dequant(planes)^T with the row scales applied after the accumulation."""
+    Y = _native_linear(_LINEAR, X, hi, lo, scales, N, K, 0, out, workspace, 0, 0)
+    if Y is not None:
+        return Y
     need = lambda M: fp6_linear_workspace_bytes(M, N, K)
     return _linear("fp6_linear", need, X, hi, lo, scales, N, K, out, workspace)
 
@@ -407,6 +437,9 @@ def fp6_linear_group_workspace_bytes(M: int, shapes) -> int:
 def fp6_linear_group(layers, outs=None, workspace: Optional[torch.Tensor] = None):
     """Independent layers [(X, hi, lo, scales, N, K), ...] on activations of one height M in one call
     (one launch for M <= 16 and a common K).  Returns the list of Y tensors."""
+    ys = _native_group(layers, outs, workspace)
+    if ys is not None:
+        return ys
     arr, M, ys = _group_array(layers, outs=outs)
     need = int(lib().fp6_linear_group_workspace_bytes(M, arr, len(layers)))
     if workspace is None:
@@ -445,6 +478,9 @@ def fp6_linear_fgq(X: torch.Tensor, hi: torch.Tensor, lo: torch.Tensor, scales: 
                    block: int, variant: int = FP6_VARIANT_AUTO, split_k: int = 0,
                    out: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Y[M,N] with block scales applied to each block's product sum before the accumulation."""
+    Y = _native_linear(_FGQ, X, hi, lo, scales, N, K, block, out, workspace, variant, split_k)
+    if Y is not None:
+        return Y
     if block <= 0:
         raise Fp6Error("block must divide K")
     need = lambda M: fp6_linear_fgq_workspace_bytes(M, N, K, block, variant, split_k)
@@ -473,6 +509,9 @@ def fp5_linear_workspace_bytes(M: int, N: int, K: int, variant: int = FP6_VARIAN
 def fp5_linear(X: torch.Tensor, hi: torch.Tensor, lo: torch.Tensor, scales: torch.Tensor, N: int, K: int,
                variant: int = FP6_VARIANT_AUTO, split_k: int = 0, out: Optional[torch.Tensor] = None,
                workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
+    Y = _native_linear(_FP5, X, hi, lo, scales, N, K, 0, out, workspace, variant, split_k)
+    if Y is not None:
+        return Y
     need = lambda M: fp5_linear_workspace_bytes(M, N, K, variant, split_k)
     return _linear("fp5_linear", need, X, hi, lo, scales, N, K, out, workspace, (variant, split_k), lo_div=8)
 
@@ -498,6 +537,9 @@ def fp6_linear_v2_workspace_bytes(M: int, N: int, K: int, variant: int = FP6_VAR
 def fp6_linear_v2(X: torch.Tensor, hi: torch.Tensor, lo: torch.Tensor, scales: torch.Tensor, N: int, K: int,
                   variant: int = FP6_VARIANT_AUTO, split_k: int = 0, out: Optional[torch.Tensor] = None,
                   workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
+    Y = _native_linear(_V2, X, hi, lo, scales, N, K, 0, out, workspace, variant, split_k)
+    if Y is not None:
+        return Y
     need = lambda M: fp6_linear_v2_workspace_bytes(M, N, K, variant, split_k)
     return _linear("fp6_linear_v2", need, X, hi, lo, scales, N, K, out, workspace, (variant, split_k))
 
@@ -506,6 +548,9 @@ def fp6_linear_v2_bf16(X: torch.Tensor, hi: torch.Tensor, lo: torch.Tensor, scal
                        variant: int = FP6_VARIANT_AUTO, split_k: int = 0, out: Optional[torch.Tensor] = None,
                        workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Layout-2 planes against bf16 activations; returns bf16."""
+    Y = _native_linear(_V2_BF16, X, hi, lo, scales, N, K, 0, out, workspace, variant, split_k)
+    if Y is not None:
+        return Y
     need = lambda M: fp6_linear_v2_workspace_bytes(M, N, K, variant, split_k)
     return _linear("fp6_linear_v2_bf16", need, X, hi, lo, scales, N, K, out, workspace, (variant, split_k),
                    dtype=torch.bfloat16)

@@ -16,6 +16,23 @@ FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
          "-Wall", "-Wno-unused-function"]
 
 
+NATIVE = os.path.join(HERE, "_native.so")          # marshalling of the hot-path calls for Python
+
+
+def build_native() -> str:
+    import sysconfig
+    import torch
+    root = os.path.dirname(torch.__file__)
+    include, libs = os.path.join(root, "include"), os.path.join(root, "lib")
+    subprocess.run(["hipcc", "-x", "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+                    "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+                    "-isystem", include, "-isystem", os.path.join(include, "torch", "csrc", "api", "include"),
+                    "-isystem", "/opt/rocm/include", "-isystem", sysconfig.get_paths()["include"],
+                    os.path.join(CSRC, "fp6_python.cpp"), "-o", NATIVE,
+                    "-L" + libs, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"], check=True)
+    return NATIVE
+
+
 def build(verbose: bool = False, extra_flags=(), lib: str = LIB, tag: str = "") -> str:
     """Compile every source and link `lib`.  extra_flags / tag are for tuning builds (-D switches)."""
     os.makedirs(OBJ, exist_ok=True)
@@ -26,8 +43,11 @@ def build(verbose: bool = False, extra_flags=(), lib: str = LIB, tag: str = "") 
         return obj
 
     with ThreadPoolExecutor(max_workers=8) as ex:
+        native = ex.submit(build_native) if lib == LIB else None
         objs = list(ex.map(_compile, SOURCES))
     subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", lib, *objs], check=True)
+    if native:
+        native.result()
     if verbose:
         print("built", lib)
     return lib
