@@ -200,14 +200,22 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
               hint_half = (variant >> 24) & 0x3, hint_gbn = (variant >> 26) & 0xF, hint_kw = (variant >> 30) & 0x1;
     const int variant_hints = variant >> 8;
     variant &= 0xFF;
+    bool two_blocks = false;           // the streaming kernel with two blocks of 16 rows, for the formats beside layout 1 of FP6
     if (variant == FP6_VARIANT_AUTO) {
+        // FP5 and plane layout 2 at 17 to 32 rows.  Against the tiled kernel (4282 random layers; time of the streaming one by 4096
+        // weights): up to 7168 of them 0.82, 0.9 % of the layers more than 3 % slower; above, only with 160 to 256 channel blocks,
+        // that is a workgroup for most compute units without a split, 0.80 up to 21504 (none slower), 0.9 to 1.1 elsewhere.  Later, on 300
+        // other layers, 0.82; four of them more than 3 % slower (28 x 2176 x 13248 13.7 / 15.0 us, 306 workgroups).
+        const int64_t wtiles = nblocks * ktiles;
+        two_blocks = M > 16 && M <= 32 && format != kE3M2 && !block && !variant_hints && !split_k &&
+                     (wtiles <= 7168 || (nblocks >= 160 && nblocks <= 256 && wtiles <= 21504));
         // The streaming kernel reads X once per wavefront and tile: unbeatable up to 16 rows, still ahead of the
         // tiled kernel up to 32 rows on layers of up to 72 M weights (4096 x 4096: 9.6 against 12.8 us), behind it
         // on larger ones (28672 x 8192: 48 against 40 us), where the tiled kernel's shared X tile pays.
         // Up to 64 rows it stays ahead where there are at most 64 channel blocks, too few tiles for the tiled kernel
         // (M = 64: 15.4 against 16.2 us at 4096 x 4096, 23.3 against 27.0 at 4096 x 11008; behind from 5120 channels on).
         const bool plain_call = format == kE3M2 && !block && !(variant_hints);
-        const bool stream = M <= 16 || (M <= 32 && plain_call && N * K <= kModel.stream_to_32_weights) ||
+        const bool stream = M <= 16 || two_blocks || (M <= 32 && plain_call && N * K <= kModel.stream_to_32_weights) ||
                             (M <= 64 && plain_call && nblocks <= kModel.stream_to_64_blocks && N * K <= kModel.stream_to_64_weights);
         variant = stream ? FP6_VARIANT_DECODE : FP6_VARIANT_GEMM;
     }
@@ -263,9 +271,9 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
             (hint_depth && !(p.half_tiles ? (hint_depth == 4 || hint_depth == 6 || hint_depth == 8)
                                           : (hint_depth >= 2 && hint_depth <= 4))))
             return false;
-        // M > 16: the wavefronts take two or four blocks of 16 rows of X (plain FP6, default configuration only)
+        // M > 16: the wavefronts take two or four blocks of 16 rows of X (plain FP6, default configuration; two also where the rule above says)
         p.block_m = M <= 16 ? 16 : (M <= 32 ? 32 : 64);
-        if (M > 16 && (!plain || hint_waves || hint_depth || p.half_tiles || hint_meet == 2)) return false;
+        if (M > 16 && ((!plain && !two_blocks) || hint_waves || hint_depth || p.half_tiles || hint_meet == 2)) return false;
         p.waves = hint_waves ? hint_waves : 4;
         p.depth = hint_depth ? hint_depth : (p.block_m == 64 ? 3 : 4);      // four row blocks per wavefront: ring of three
         tiles = nblocks;

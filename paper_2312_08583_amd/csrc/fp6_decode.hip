@@ -688,7 +688,14 @@ hipError_t launch_decode(const LinearPlan& p, const uint16_t* X, int64_t M, cons
                          const uint16_t* scales, int64_t N, int64_t K, uint16_t* Y, void* workspace,
                          hipStream_t stream)
 {
-    if (p.block_m == 32) return launch_decode_t<4, 4, kBiasShift, false, kE3M2, 2>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+    if (p.block_m == 32) {
+        switch (p.format) {
+            case kE3M2H: return launch_decode_t<4, 4, kBiasShift, false, kE3M2H, 2>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+            case kE3M2B: return launch_decode_t<4, 4, kBiasShift, false, kE3M2B, 2>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+            case kE3M1: return launch_decode_t<4, 4, kBiasShift, false, kE3M1, 2>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+            default: return launch_decode_t<4, 4, kBiasShift, false, kE3M2, 2>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+        }
+    }
     if (p.block_m == 64) return launch_decode_t<4, 3, kBiasShift, false, kE3M2, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
     if (p.half_tiles && p.format == kE3M1) return launch_decode_half_t<4, 4, kE3M1>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
     if (p.half_tiles) {

@@ -1,0 +1,49 @@
+"""Streaming kernel at 17 to 32 rows for FP5 and plane layout 2: where the planner takes it, and the results against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2312_08583_amd as P
+from oracle import fp6_oracle as O
+from paper_2312_08583_amd import binding as B
+from paper_2312_08583_amd import inputs
+
+from gpu_util import assert_y_close, to_np16
+
+DEV = "cuda"
+FORMATS = {"fp5": 5, "v2": 7, "bf16": 8}
+
+
+@pytest.mark.parametrize("fmt", list(FORMATS))
+def test_where_the_planner_takes_it(fmt):
+    plan = lambda M, nblocks, ktiles, **kw: P.fp6_linear_plan(M, nblocks * 64, ktiles * 64, format=FORMATS[fmt], **kw)
+    for M, nblocks, ktiles in [(17, 16, 16), (32, 112, 64), (24, 128, 56), (20, 160, 134), (32, 256, 84), (17, 400, 16)]:
+        p = plan(M, nblocks, ktiles)
+        assert (p["variant"], p["block_m"]) == (B.FP6_VARIANT_DECODE, 32)
+    for M, nblocks, ktiles in [(33, 16, 16), (32, 112, 65), (24, 159, 134), (24, 257, 84), (32, 256, 85)]:
+        assert plan(M, nblocks, ktiles)["variant"] == B.FP6_VARIANT_GEMM
+    assert plan(24, 64, 64, split_k=2)["variant"] == B.FP6_VARIANT_GEMM            # forced splits stay with the tiled kernel
+    with pytest.raises(P.Fp6Error):                                                # and forcing the kernel is refused as before
+        plan(24, 64, 64, variant=B.FP6_VARIANT_DECODE)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fmt", list(FORMATS))
+@pytest.mark.parametrize("M,N,K", [(17, 192, 64), (32, 1088, 832), (25, 1024, 4096), (31, 10304, 1152), (18, 16448, 704), (24, 2752, 9344)])
+def test_two_blocks_of_rows(fmt, M, N, K):
+    assert P.fp6_linear_plan(M, N, K, format=FORMATS[fmt])["variant"] == B.FP6_VARIANT_DECODE
+    W = inputs.weight(N, K, seed=9600 + M, sigma=0.02, outlier_frac=0.001, device=DEV)
+    X = (inputs.activation_bf16 if fmt == "bf16" else inputs.activation)(M, K, seed=9700 + M, device=DEV)
+    planes = (P.fp5_quantize_pack if fmt == "fp5" else P.fp6_quantize_pack_v2)(W)
+    fn = {"fp5": P.fp5_linear, "v2": P.fp6_linear_v2, "bf16": P.fp6_linear_v2_bf16}[fmt]
+    Y = [fn(X, *planes, N, K), fn(X, *planes, N, K)]
+    assert torch.equal(Y[0].view(torch.int16), Y[1].view(torch.int16))
+    pick = torch.arange(N) if N <= 1100 else torch.cat([torch.arange(96), torch.arange(N - 96, N), torch.arange(100, N - 100, N // 200)])
+    wb, xb = to_np16(W[pick.to(DEV)].contiguous()), X.cpu().view(torch.int16).numpy().view(np.uint16)
+    Yref = {"fp5": O.linear5, "v2": O.linear, "bf16": O.linear_bf16}[fmt](xb, *(O.quantize5 if fmt == "fp5" else O.quantize)(wb))
+    y = Y[0].cpu()[:, pick]
+    if fmt == "bf16":
+        yd = y.double().numpy()               # half a unit in the last of 8 significant bits, and the fp32 sums
+        assert (np.abs(yd - Yref) <= 2.0 ** -8 * np.abs(Yref) + 1e-4 * (np.abs(Yref) + np.sqrt(np.mean(Yref ** 2)))).all()
+    else:
+        assert_y_close(y, Yref, (fmt, M, N, K))
