@@ -133,7 +133,11 @@ __device__ __forceinline__ void decode_block(
     int split_k, int pairwise, int gshift, int nb, int s, int gnb)
 {
     constexpr bool LINES = EXACT && MB > 1;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // Four blocks of rows in the short form are left to the compiler, tiles addressed per lane: 244 registers.  Held like the rest they took
+    // 264, one wavefront to a SIMD instead of two, and 1.02 to 1.03 of the time in slices of one or two and of five to eight k tiles (2000
+    // layers; 64 x 512 x 64 4.4 / 4.5 us), 1.2 with more than 256 workgroups.
+    constexpr bool HELD = MB < 4 || EXACT;
+    const int lane = threadIdx.x & 63, wave = HELD ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : (int)threadIdx.x >> 6;
     const int ktiles = K / kTile;
     const int kt_begin = slice_begin(ktiles, split_k, s), kt_end = slice_begin(ktiles, split_k, s + 1);
     static_assert(MB == 1 || !FGQ, "several row blocks: row-wise scales only");
@@ -225,9 +229,9 @@ __device__ __forceinline__ void decode_block(
                     const int k = tile_at(j0 + u + D - 1);
                     raw[(u + D - 1) % D] = load_tile<FMT>(hi, lo, tile0 + k, lane);
                     fetch_x((u + D - 1) % D, k);
-                    __builtin_amdgcn_sched_barrier(0);          // (left alone, the compiler sinks the loads towards their use)
+                    if (HELD) __builtin_amdgcn_sched_barrier(0);          // (left alone, the compiler sinks the loads towards their use)
                     mac(u, xf[u], tile_at(j0 + u));
-                    if (!EXACT) __builtin_amdgcn_sched_barrier(0);
+                    if (HELD && !EXACT) __builtin_amdgcn_sched_barrier(0);
                 }
             }
             if constexpr (!EXACT) {
@@ -391,7 +395,7 @@ __device__ __forceinline__ void decode_block(
 }
 
 template <int WAVES, int D, int DQ, bool FGQ, int FMT, int MB, bool EXACT>
-__global__ __launch_bounds__(WAVES * 64, WAVES != 4 || MB > 1 || EXACT ? 1 : FGQ || layout2(FMT) ? 3 : 4) void decode_kernel(
+__global__ __launch_bounds__(WAVES * 64, WAVES != 4 || EXACT || MB == 4 ? 1 : MB == 2 ? 2 : FGQ || layout2(FMT) ? 3 : 4) void decode_kernel(
     const uint16_t* __restrict__ X, int M, const u32x4* __restrict__ hi, const u32x4* __restrict__ lo,
     const uint16_t* __restrict__ scales, int N, int K, uint16_t* __restrict__ Y,
     float4v* __restrict__ partials, uint32_t* __restrict__ counters, unsigned long long* __restrict__ slots,
@@ -649,8 +653,8 @@ static hipError_t launch_decode_half_t(const LinearPlan& p, const uint16_t* X, i
 }
 
 // Which of the two forms of decode_block a launch takes.  Straight code for the last tiles needs registers (172 to 208 of a lane's
-// 512, 340 and 512 with several row blocks; the short form 104 to 136, 184 and 264): it is for launches whose workgroups then still
-// fit the chip at once, two to a compute unit or one.  With three tiles or less to a wavefront there is nothing but last tiles, and the code
+// 512, 332 to 392 and 512 with two and four row blocks; the short form 104 to 136, 158 to 190 and 244): it is for launches whose workgroups
+// then still fit the chip at once, two to a compute unit or one.  With three tiles or less to a wavefront there is nothing but last tiles, and the code
 // of their number is fetched for one use.  Measured against one form for all, time by tiles to a wavefront: 2 1.04, 2 to 3 1.00, 3 to 4 0.95,
 // 4 to 6 0.90, above 0.94 (363 random layers of 1 to 16 rows, all formats); with 17 to 64 rows 1.03, 0.99, 0.98, 0.98 and 0.95 (46 layers);
 // 618 and 648 workgroups of it 1.15 and 1.21.
