@@ -657,10 +657,11 @@ static hipError_t launch_decode_half_t(const LinearPlan& p, const uint16_t* X, i
 // then still fit the chip at once, two to a compute unit or one.  With three tiles or less to a wavefront there is nothing but last tiles, and the code
 // of their number is fetched for one use.  Measured against one form for all, time by tiles to a wavefront: 2 1.04, 2 to 3 1.00, 3 to 4 0.95,
 // 4 to 6 0.90, above 0.94 (363 random layers of 1 to 16 rows, all formats); with 17 to 64 rows 1.03, 0.99, 0.98, 0.98 and 0.95 (46 layers);
-// 618 and 648 workgroups of it 1.15 and 1.21.
+// 618 and 648 workgroups of it 1.15 and 1.21.  With two row blocks the line is at slices of 15 k tiles (1.01 to 1.02 of the short form's time
+// from 13 to 15 for FP6, 1.00 for the other formats; at 16 1.00 and 0.98; 10800 layers).
 static bool runs_exact(int64_t K, int split_k, int64_t workgroups, int mb)
 {
-    return workgroups <= (mb == 1 ? 512 : 256) && (K / kTile + split_k - 1) / split_k > 3 * 4;
+    return workgroups <= (mb == 1 ? 512 : 256) && (K / kTile + split_k - 1) / split_k > (mb == 2 ? 15 : 12);
 }
 
 template <int WAVES, int D, int DQ = kBiasShift, bool FGQ = false, int FMT = kE3M2, int MB = 1>

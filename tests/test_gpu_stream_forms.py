@@ -1,5 +1,5 @@
 """Streaming kernel: the two forms of its stream (straight code for the last tiles, or one branch to each), on both sides of the lines
-between them - three tiles to a wavefront and more, 512 workgroups (256 with several blocks of rows) and more - and every number of last
+between them - slices of 12 k tiles and more (15 with two blocks of rows), 512 workgroups (256 with several blocks of rows) and more - and every number of last
 tiles that a wavefront can be left with.  Against the oracle."""
 import numpy as np
 import pytest
@@ -52,6 +52,11 @@ def test_every_number_of_last_tiles(fmt, M, ktiles):
                                      ("fp5", 16, 513 * 64), ("fp6", 24, 256 * 64), ("fp6", 24, 257 * 64), ("fp6", 50, 257 * 64)])
 def test_as_many_workgroups_as_fit_and_one_more(fmt, M, N):
     _check(fmt, M, N, 13 * 64)
+
+
+@pytest.mark.parametrize("nblocks,ktiles", [(3, 15), (3, 16), (3, 17), (256, 16), (257, 16)])
+def test_two_blocks_of_rows_on_both_sides_of_their_lines(nblocks, ktiles):
+    _check("fp6", 25, nblocks * 64, ktiles * 64)
 
 
 @pytest.mark.parametrize("ktiles,split", [(12, 2), (26, 2), (52, 4), (39, 3)])
