@@ -202,12 +202,14 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
     variant &= 0xFF;
     bool two_blocks = false;           // the streaming kernel with two blocks of 16 rows, for the formats beside layout 1 of FP6
     if (variant == FP6_VARIANT_AUTO) {
-        // FP5 and plane layout 2 at 17 to 32 rows.  Against the tiled kernel (4282 random layers; time of the streaming one by 4096
-        // weights): up to 7168 of them 0.82, 0.9 % of the layers more than 3 % slower; above, only with 160 to 256 channel blocks,
-        // that is a workgroup for most compute units without a split, 0.80 up to 21504 (none slower), 0.9 to 1.1 elsewhere.  Later, on 300
-        // other layers, 0.82; four of them more than 3 % slower (28 x 2176 x 13248 13.7 / 15.0 us, 306 workgroups).
+        // FP5 and plane layout 2 at 17 to 32 rows, against the tiled kernel.  By weights: up to 7168 times 4096 of them, and up to 21504
+        // times with 160 to 256 channel blocks, a workgroup for most compute units without a split (elsewhere 0.9 to 1.1 of the time).  With
+        // more than 256 channel blocks, which run the short form of the stream, not up to six k tiles: planes from HBM 1.00 of the time (1600 layers, 10 %
+        // more than 3 % slower), from the last cache 1.09 (2200, 96 %; 24 x 27008 x 256 6.5 / 7.7 us).  What stays takes 0.84 of the time from
+        // HBM (40000 random layers of 64 to 28672 channels and k, 1 % more than 3 % slower, nearly all of one k tile or up to 320 channels) and 0.89
+        // from the last cache (7 %; 28 x 2176 x 13248 13.7 / 15.0 us).
         const int64_t wtiles = nblocks * ktiles;
-        two_blocks = M > 16 && M <= 32 && format != kE3M2 && !block && !variant_hints && !split_k &&
+        two_blocks = M > 16 && M <= 32 && format != kE3M2 && !block && !variant_hints && !split_k && (nblocks <= 256 || ktiles >= 7) &&
                      (wtiles <= 7168 || (nblocks >= 160 && nblocks <= 256 && wtiles <= 21504));
         // The streaming kernel reads X once per wavefront and tile: unbeatable up to 16 rows, still ahead of the
         // tiled kernel up to 32 rows on layers of up to 72 M weights (4096 x 4096: 9.6 against 12.8 us), behind it

@@ -22,6 +22,9 @@ def test_where_the_planner_takes_it(fmt):
         assert (p["variant"], p["block_m"]) == (B.FP6_VARIANT_DECODE, 32)
     for M, nblocks, ktiles in [(33, 16, 16), (32, 112, 65), (24, 159, 134), (24, 257, 84), (32, 256, 85)]:
         assert plan(M, nblocks, ktiles)["variant"] == B.FP6_VARIANT_GEMM
+    # more channel blocks than run the straight-code form of the stream, with up to six k tiles: 1.09 of the tiled kernel's time
+    for M, nblocks, ktiles, takes in [(24, 256, 2, True), (24, 257, 6, False), (24, 257, 7, True), (24, 422, 4, False), (31, 448, 7, True)]:
+        assert (plan(M, nblocks, ktiles)["variant"] == B.FP6_VARIANT_DECODE) == takes, (M, nblocks, ktiles)
     assert plan(24, 64, 64, split_k=2)["variant"] == B.FP6_VARIANT_GEMM            # forced splits stay with the tiled kernel
     with pytest.raises(P.Fp6Error):                                                # and forcing the kernel is refused as before
         plan(24, 64, 64, variant=B.FP6_VARIANT_DECODE)
