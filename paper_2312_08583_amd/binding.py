@@ -6,7 +6,10 @@ fallback: if the library cannot be loaded, or a tensor is not on the GPU, the ca
 raises.
 """
 import ctypes
+import importlib.util
 import os
+import subprocess
+import warnings
 from typing import Optional, Tuple
 
 import torch
@@ -88,20 +91,27 @@ def _not_loaded(*_):
 
 
 # Marshalling in native code (csrc/fp6_python.cpp): the result of a plain call with its workspace, or None, and then the routines below
-# take the call: the checks are the same, allocations and errors are theirs.
+# take the call: the checks are the same, allocations and errors are theirs.  Without the module they take every call.
 _native_linear = _native_group = _not_loaded
 _LINEAR, _VARIANT, _FGQ, _FP5, _V2, _V2_BF16 = range(6)
 
 
-def _bind_native(L: ctypes.CDLL) -> None:
+def _bind_native(L: ctypes.CDLL, path: str) -> None:
     global _native_linear, _native_group
-    from . import _native
+    _native_linear = _native_group = _not_loaded
     entries = (L.fp6_linear, L.fp6_linear_variant, L.fp6_linear_fgq, L.fp5_linear, L.fp6_linear_v2, L.fp6_linear_v2_bf16,
                L.fp6_linear_group, L.fp6_linear_workspace_bytes, L.fp6_linear_variant_workspace_bytes,
                L.fp6_linear_fgq_workspace_bytes, L.fp5_linear_workspace_bytes, L.fp6_linear_v2_workspace_bytes,
                L.fp6_linear_group_workspace_bytes)
-    _native.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in entries), _check)
-    _native_linear, _native_group = _native.linear, _native.group
+    try:
+        spec = importlib.util.spec_from_file_location(__package__ + "._native", path)
+        native = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(native)
+        native.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in entries), _check)
+        _native_linear, _native_group = native.linear, native.group
+    except (ImportError, AttributeError, TypeError) as e:          # not there, not of this build, or of another version of bind()
+        warnings.warn("%s: hot-path calls are marshalled in Python, 3 to 6 us slower each (python -m paper_2312_08583_amd.build "
+                      "builds the module)" % e, RuntimeWarning, stacklevel=3)
 
 
 class Fp6Error(RuntimeError):
@@ -115,9 +125,11 @@ def lib() -> ctypes.CDLL:
         return _LIB
     from . import build as _build
     if not os.path.exists(LIB_PATH):
-        _build.build()
-    if not os.path.exists(_build.NATIVE):
-        _build.build_native()
+        try:
+            _build.build()
+        except subprocess.CalledProcessError:
+            if not os.path.exists(LIB_PATH):          # (what failed is the marshalling module)
+                raise
     L = ctypes.CDLL(LIB_PATH)
     i64, p, sz, ci = ctypes.c_int64, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int
     L.fp6_layout_version.restype = ci
@@ -184,8 +196,8 @@ def lib() -> ctypes.CDLL:
     L.fp6_linear_group.argtypes = [i64, ctypes.POINTER(LinearProblem), ci, p, sz, p]
     L.fp6_linear_plan.restype = ci
     L.fp6_linear_plan.argtypes = [ci, i64, i64, i64, i64, ci, ci, ctypes.POINTER(PlanInfo)]
-    _bind_native(L)
     _LIB = L
+    _bind_native(L, _build.native_path())
     return L
 
 

@@ -16,7 +16,9 @@ FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
          "-Wall", "-Wno-unused-function"]
 
 
-NATIVE = os.path.join(HERE, "_native.so")          # marshalling of the hot-path calls for Python
+def native_path() -> str:
+    """Marshalling of the hot-path calls for Python."""
+    return os.path.join(HERE, "_native.so")
 
 
 def build_native() -> str:
@@ -28,9 +30,9 @@ def build_native() -> str:
                     "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
                     "-isystem", include, "-isystem", os.path.join(include, "torch", "csrc", "api", "include"),
                     "-isystem", "/opt/rocm/include", "-isystem", sysconfig.get_paths()["include"],
-                    os.path.join(CSRC, "fp6_python.cpp"), "-o", NATIVE,
+                    os.path.join(CSRC, "fp6_python.cpp"), "-o", native_path(),
                     "-L" + libs, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"], check=True)
-    return NATIVE
+    return native_path()
 
 
 def build(verbose: bool = False, extra_flags=(), lib: str = LIB, tag: str = "") -> str:
