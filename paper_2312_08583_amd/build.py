@@ -17,8 +17,10 @@ FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
 
 
 def native_path() -> str:
-    """Marshalling of the hot-path calls for Python."""
-    return os.path.join(HERE, "_native.so")
+    """Marshalling of the hot-path calls for Python, built for this Python and this torch: no other finds it under this name."""
+    import sysconfig
+    import torch
+    return os.path.join(HERE, "_native-torch" + torch.__version__ + sysconfig.get_config_var("EXT_SUFFIX"))
 
 
 def build_native() -> str:
@@ -26,13 +28,20 @@ def build_native() -> str:
     import torch
     root = os.path.dirname(torch.__file__)
     include, libs = os.path.join(root, "include"), os.path.join(root, "lib")
-    subprocess.run(["hipcc", "-x", "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
-                    "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
-                    "-isystem", include, "-isystem", os.path.join(include, "torch", "csrc", "api", "include"),
-                    "-isystem", "/opt/rocm/include", "-isystem", sysconfig.get_paths()["include"],
-                    os.path.join(CSRC, "fp6_python.cpp"), "-o", native_path(),
-                    "-L" + libs, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"], check=True)
-    return native_path()
+    path = native_path()
+    part = "%s.%d" % (path, os.getpid())          # whole when it appears under its name: other processes may be importing it
+    try:
+        subprocess.run(["hipcc", "-x", "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+                        "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+                        "-isystem", include, "-isystem", os.path.join(include, "torch", "csrc", "api", "include"),
+                        "-isystem", "/opt/rocm/include", "-isystem", sysconfig.get_paths()["include"],
+                        os.path.join(CSRC, "fp6_python.cpp"), "-o", part,
+                        "-L" + libs, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"], check=True)
+        os.replace(part, path)
+    finally:
+        if os.path.exists(part):
+            os.remove(part)
+    return path
 
 
 def build(verbose: bool = False, extra_flags=(), lib: str = LIB, tag: str = "") -> str:

@@ -47,3 +47,34 @@ def test_the_module_that_was_built_is_loaded(fresh):
         warnings.simplefilter("error")
         B.lib()
     assert B._native_linear is not B._not_loaded and B._native_group is not B._not_loaded
+
+
+def test_a_module_of_another_torch_or_python_is_not_taken(monkeypatch):
+    import sysconfig
+    import torch
+    here = hip_build.native_path()
+    assert here.endswith(sysconfig.get_config_var("EXT_SUFFIX")) and os.path.dirname(here) == hip_build.HERE
+    monkeypatch.setattr(torch, "__version__", "2.9.1+rocm6.4")
+    assert hip_build.native_path() != here
+
+
+def test_a_module_appears_whole_or_not_at_all(monkeypatch, tmp_path):
+    path = tmp_path / "_native.so"
+    path.write_bytes(b"the one before")
+    monkeypatch.setattr(hip_build, "native_path", lambda: str(path))
+
+    status = [1, 0]
+
+    def link(cmd, check):
+        with open(cmd[cmd.index("-o") + 1], "wb") as f:
+            f.write(b"half")
+            assert path.read_bytes() == b"the one before"          # what another process would import now
+            f.write(b" and half")
+        if status.pop(0):
+            raise subprocess.CalledProcessError(1, cmd)
+    monkeypatch.setattr(subprocess, "run", link)
+    with pytest.raises(subprocess.CalledProcessError):
+        hip_build.build_native()
+    assert [p.read_bytes() for p in tmp_path.iterdir()] == [b"the one before"]
+    hip_build.build_native()
+    assert [p.read_bytes() for p in tmp_path.iterdir()] == [b"half and half"]
