@@ -152,7 +152,8 @@ PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t count)
         }
         Py_END_ALLOW_THREADS
     } catch (...) {
-        Py_RETURN_NONE;          // (nothing below the checks throws but the allocation of Y)
+        Py_XDECREF(result);          // (the allocation of Y threw, or the look-up of the stream behind it)
+        Py_RETURN_NONE;
     }
     if (status == FP6_OK) return result;
     Py_DECREF(result);
