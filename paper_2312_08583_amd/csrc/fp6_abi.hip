@@ -247,7 +247,8 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
     // four give twice the workgroups where there are few (measured: 40 against 47 us at 32 x 28672 x 8192, 24
     // against 30 us at 512 x 1024 x 8192, 20.7 against 30 us at 128 x 5120 x 5120).  The cost model below chooses.
     const bool plain = format == kE3M2 && !block && !hint_dequant;
-    // forced splits and plans have even slices; an ablation is compared with the method, and planned like it
+    // Forced splits and plans have even slices.  An ablation is compared with the method: up to 16 rows it has its plan and its form of the
+    // stream.  Its tiled kernels have 512 channels and 32, 64 or 128 rows a workgroup: a comparison there forces the method's to that.
     even_only = even_only || split_k || (variant_hints & ~(0x3 << 14));
     const bool narrow_ok = !hint_dequant && variant == FP6_VARIANT_GEMM;      // every format but the ablations
     int64_t gbn = hint_gbn ? hint_gbn : 8;

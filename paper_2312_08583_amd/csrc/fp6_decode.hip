@@ -679,7 +679,7 @@ static hipError_t launch_decode_t(const LinearPlan& p, const uint16_t* X, int64_
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(WAVES * 64), lds, stream, X, (int)M, (const u32x4*)hi, (const u32x4*)lo, scales,
                            (int)N, (int)K, Y, partials, counters, slots, p.split_k, p.pairwise, p.gshift);
     };
-    if constexpr (WAVES == 4 && DQ == kBiasShift && D == (MB == 4 ? 3 : 4)) {
+    if constexpr (WAVES == 4 && D == (MB == 4 ? 3 : 4)) {
         if (runs_exact(K, p.split_k, grid, MB)) {
             launch(decode_kernel<WAVES, D, DQ, FGQ, FMT, MB, true>);
             return hipGetLastError();

@@ -52,3 +52,10 @@ def test_short_forms_of_several_row_blocks_leave_room_for_two_wavefronts():
     regs = _kernel_field("fp6_decode.hip", "vgpr_count")
     short = {k: v for k, v in regs.items() if re.search(r"decode_kernelILi4ELi[34]ELi0ELb0ELi\dELi[24]ELb0E", k)}
     assert len(short) == 5 and all(v <= 256 for v in short.values()), short
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+def test_the_ablations_have_the_stream_of_the_method():
+    """Both forms of the stream for each unpack: the ablations are timed against the method, and the unpack is to be the only difference."""
+    forms = set(re.findall(r"decode_kernelILi4ELi4ELi(\d)ELb0ELi6ELi1ELb(\d)E", " ".join(_kernel_field("fp6_decode.hip", "vgpr_count"))))
+    assert forms == {(dq, exact) for dq in "012" for exact in "01"}

@@ -59,6 +59,17 @@ def test_two_blocks_of_rows_on_both_sides_of_their_lines(nblocks, ktiles):
     _check("fp6", 25, nblocks * 64, ktiles * 64)
 
 
+@pytest.mark.parametrize("dequant", [1, 2])
+@pytest.mark.parametrize("ktiles", KTILES)
+def test_the_ablations_run_the_forms_of_the_method(dequant, ktiles):
+    """The same products times powers of two in the same order: bit for bit the method's results."""
+    M, N, K = 8, 192, ktiles * 64
+    W, X = inputs.weight(N, K, seed=9100 + K, sigma=0.02, outlier_frac=0.001, device=DEV), inputs.activation(M, K, seed=9200 + M, device=DEV)
+    planes = P.fp6_quantize_pack(W)
+    Y = [P.fp6_linear_variant(X, *planes, N, K, B.FP6_VARIANT_DECODE | hint, 1) for hint in (0, B.FP6_HINT_DEQUANT(dequant))]
+    assert torch.equal(*Y)
+
+
 @pytest.mark.parametrize("ktiles,split", [(12, 2), (26, 2), (52, 4), (39, 3)])
 def test_slices(ktiles, split):
     _check("fp6", 12, 320, ktiles * 64, split=split)
