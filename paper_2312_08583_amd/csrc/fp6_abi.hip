@@ -434,7 +434,7 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
             const int64_t mblk = (M + p.block_m - 1) / p.block_m;
             p.block_m = (int)((M + 16 * mblk - 1) / (16 * mblk) * 16);
         }
-        p.depth = p.kw == 2 ? 2 : gbn == 8 ? (p.block_m > 64 ? 3 : 4) : (p.block_m == 128 ? 2 : (p.block_m > 32 ? 3 : 4));
+        p.depth = ring_stages(p.block_m, (int)gbn, p.kw);
         p.waves = (int)gbn * p.kw;
         tiles = ((M + p.block_m - 1) / p.block_m) * ((nblocks + gbn - 1) / gbn);
         regs_per_tile = (int64_t)(p.block_m / 16) * 4 * 64 * gbn;

@@ -199,8 +199,6 @@ __device__ __forceinline__ void unpack_step(const TileRaw& r, int q, int c, uint
 // sign/exponent bits of string dwords 4 and 5, which a shift by two puts in place.  Merging the
 // planes back costs 11 logic operations per 32 weights.
 typedef uint32_t u32x6 __attribute__((ext_vector_type(6)));
-typedef _Float16 half32 __attribute__((ext_vector_type(32)));
-typedef __bf16 bf16x32 __attribute__((ext_vector_type(32)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 constexpr uint32_t kSE0 = 0x3CF3CF3Cu, kSE1 = 0xCF3CF3CFu, kSE2 = 0xF3CF3CF3u;   // sign/exponent positions of string dwords j % 3 = 0, 1, 2

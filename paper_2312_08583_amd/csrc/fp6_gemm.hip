@@ -10,23 +10,19 @@ hipError_t launch_gemm(const LinearPlan& p, const uint16_t* X, int64_t M, const 
     if (p.block_m & (p.block_m - 1)) return launch_gemm_heights(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
     if (p.format != kE3M2 || p.gshift >= 0 || p.dequant != kBiasShift)
         return launch_gemm_variant(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
-    // Four-wavefront workgroups are built so that two fit a compute unit (at most 256 registers per lane and
-    // 80 KB of LDS: a ring of 4, 3 and 2 stages at 32, 64 and 128 rows), i.e. two wavefronts per SIMD as with
-    // eight-wavefront workgroups; measured 4-10 % faster than deeper rings with one workgroup per unit.
-    // Two K-ways inside a workgroup of 128 x 256: eight wavefronts, a ring of two stages of 56 KB.
     if (p.gbn == 4 && p.kw == 2)
-        return launch_gemm_t<128, 2, kBiasShift, false, kE3M2, 4, 2>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+        return launch_gemm_t<128, kBiasShift, false, kE3M2, 4, 2>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
     if (p.gbn == 4) {
         switch (p.block_m) {
-            case 32: return launch_gemm_t<32, 4, kBiasShift, false, kE3M2, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
-            case 64: return launch_gemm_t<64, 3, kBiasShift, false, kE3M2, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
-            default: return launch_gemm_t<128, 2, kBiasShift, false, kE3M2, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+            case 32: return launch_gemm_t<32, kBiasShift, false, kE3M2, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+            case 64: return launch_gemm_t<64, kBiasShift, false, kE3M2, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+            default: return launch_gemm_t<128, kBiasShift, false, kE3M2, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
         }
     }
     switch (p.block_m) {
-        case 32: return launch_gemm_t<32, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
-        case 64: return launch_gemm_t<64, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
-        default: return launch_gemm_t<128, 3>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+        case 32: return launch_gemm_t<32>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+        case 64: return launch_gemm_t<64>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+        default: return launch_gemm_t<128>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
     }
 }
 

@@ -8,13 +8,13 @@ hipError_t launch_gemm_bf16(const LinearPlan& p, const uint16_t* X, int64_t M, c
                             hipStream_t stream)
 {
     if (p.gbn == 4) {
-        if (p.block_m == 32) return launch_gemm_t<32, 4, kBiasShift, false, kE3M2B, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
-        if (p.block_m == 64) return launch_gemm_t<64, 3, kBiasShift, false, kE3M2B, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
-        return launch_gemm_t<128, 2, kBiasShift, false, kE3M2B, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+        if (p.block_m == 32) return launch_gemm_t<32, kBiasShift, false, kE3M2B, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+        if (p.block_m == 64) return launch_gemm_t<64, kBiasShift, false, kE3M2B, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+        return launch_gemm_t<128, kBiasShift, false, kE3M2B, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
     }
-    if (p.block_m == 32) return launch_gemm_t<32, 4, kBiasShift, false, kE3M2B>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
-    if (p.block_m == 64) return launch_gemm_t<64, 4, kBiasShift, false, kE3M2B>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
-    return launch_gemm_t<128, 3, kBiasShift, false, kE3M2B>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+    if (p.block_m == 32) return launch_gemm_t<32, kBiasShift, false, kE3M2B>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+    if (p.block_m == 64) return launch_gemm_t<64, kBiasShift, false, kE3M2B>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+    return launch_gemm_t<128, kBiasShift, false, kE3M2B>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
 }
 
 }  // namespace fp6

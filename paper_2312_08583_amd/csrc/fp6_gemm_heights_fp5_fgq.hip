@@ -6,21 +6,21 @@ namespace fp6 {
 hipError_t launch_gemm_heights_fp5_fgq(const LinearPlan& p, const uint16_t* X, int64_t M, const void* hi, const void* lo,
                                const uint16_t* scales, int64_t N, int64_t K, uint16_t* Y, void* workspace, hipStream_t stream)
 {
-    if (p.gshift >= 0 && p.gbn == 4) return launch_gemm_t<48, 3, kBiasShift, true, kE3M2, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
-    if (p.gshift >= 0) return launch_gemm_t<48, 4, kBiasShift, true, kE3M2>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+    if (p.gshift >= 0 && p.gbn == 4) return launch_gemm_t<48, kBiasShift, true, kE3M2, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+    if (p.gshift >= 0) return launch_gemm_t<48, kBiasShift, true, kE3M2>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
     if (p.gbn == 4) {
         switch (p.block_m) {
-            case 48: return launch_gemm_t<48, 3, kBiasShift, false, kE3M1, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
-            case 80: return launch_gemm_t<80, 3, kBiasShift, false, kE3M1, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
-            case 96: return launch_gemm_t<96, 3, kBiasShift, false, kE3M1, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
-            default: return launch_gemm_t<112, 3, kBiasShift, false, kE3M1, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+            case 48: return launch_gemm_t<48, kBiasShift, false, kE3M1, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+            case 80: return launch_gemm_t<80, kBiasShift, false, kE3M1, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+            case 96: return launch_gemm_t<96, kBiasShift, false, kE3M1, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+            default: return launch_gemm_t<112, kBiasShift, false, kE3M1, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
         }
     }
     switch (p.block_m) {
-        case 48: return launch_gemm_t<48, 4, kBiasShift, false, kE3M1>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
-        case 80: return launch_gemm_t<80, 3, kBiasShift, false, kE3M1>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
-        case 96: return launch_gemm_t<96, 3, kBiasShift, false, kE3M1>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
-        default: return launch_gemm_t<112, 3, kBiasShift, false, kE3M1>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+        case 48: return launch_gemm_t<48, kBiasShift, false, kE3M1>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+        case 80: return launch_gemm_t<80, kBiasShift, false, kE3M1>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+        case 96: return launch_gemm_t<96, kBiasShift, false, kE3M1>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+        default: return launch_gemm_t<112, kBiasShift, false, kE3M1>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
     }
 }
 

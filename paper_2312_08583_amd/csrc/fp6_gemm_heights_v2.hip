@@ -8,33 +8,33 @@ hipError_t launch_gemm_heights_v2(const LinearPlan& p, const uint16_t* X, int64_
 {
     if (p.format == kE3M2B && p.gbn == 4) {
         switch (p.block_m) {
-            case 48: return launch_gemm_t<48, 3, kBiasShift, false, kE3M2B, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
-            case 80: return launch_gemm_t<80, 3, kBiasShift, false, kE3M2B, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
-            case 96: return launch_gemm_t<96, 3, kBiasShift, false, kE3M2B, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
-            default: return launch_gemm_t<112, 3, kBiasShift, false, kE3M2B, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+            case 48: return launch_gemm_t<48, kBiasShift, false, kE3M2B, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+            case 80: return launch_gemm_t<80, kBiasShift, false, kE3M2B, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+            case 96: return launch_gemm_t<96, kBiasShift, false, kE3M2B, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+            default: return launch_gemm_t<112, kBiasShift, false, kE3M2B, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
         }
     }
     if (p.format == kE3M2B) {
         switch (p.block_m) {
-            case 48: return launch_gemm_t<48, 4, kBiasShift, false, kE3M2B>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
-            case 80: return launch_gemm_t<80, 3, kBiasShift, false, kE3M2B>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
-            case 96: return launch_gemm_t<96, 3, kBiasShift, false, kE3M2B>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
-            default: return launch_gemm_t<112, 3, kBiasShift, false, kE3M2B>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+            case 48: return launch_gemm_t<48, kBiasShift, false, kE3M2B>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+            case 80: return launch_gemm_t<80, kBiasShift, false, kE3M2B>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+            case 96: return launch_gemm_t<96, kBiasShift, false, kE3M2B>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+            default: return launch_gemm_t<112, kBiasShift, false, kE3M2B>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
         }
     }
     if (p.gbn == 4) {
         switch (p.block_m) {
-            case 48: return launch_gemm_t<48, 3, kBiasShift, false, kE3M2H, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
-            case 80: return launch_gemm_t<80, 3, kBiasShift, false, kE3M2H, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
-            case 96: return launch_gemm_t<96, 3, kBiasShift, false, kE3M2H, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
-            default: return launch_gemm_t<112, 3, kBiasShift, false, kE3M2H, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+            case 48: return launch_gemm_t<48, kBiasShift, false, kE3M2H, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+            case 80: return launch_gemm_t<80, kBiasShift, false, kE3M2H, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+            case 96: return launch_gemm_t<96, kBiasShift, false, kE3M2H, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+            default: return launch_gemm_t<112, kBiasShift, false, kE3M2H, 4>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
         }
     }
     switch (p.block_m) {
-        case 48: return launch_gemm_t<48, 4, kBiasShift, false, kE3M2H>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
-        case 80: return launch_gemm_t<80, 3, kBiasShift, false, kE3M2H>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
-        case 96: return launch_gemm_t<96, 3, kBiasShift, false, kE3M2H>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
-        default: return launch_gemm_t<112, 3, kBiasShift, false, kE3M2H>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+        case 48: return launch_gemm_t<48, kBiasShift, false, kE3M2H>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+        case 80: return launch_gemm_t<80, kBiasShift, false, kE3M2H>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+        case 96: return launch_gemm_t<96, kBiasShift, false, kE3M2H>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
+        default: return launch_gemm_t<112, kBiasShift, false, kE3M2H>(p, X, M, hi, lo, scales, N, K, Y, workspace, stream);
     }
 }
 

@@ -91,7 +91,7 @@ __device__ __forceinline__ void wait_vmcnt()
 // from the workspace into LDS: where K has to be split to fill the chip, half of the partial sums never leave the
 // compute unit.
 template <int BM, int D, int DQ, bool FGQ, int FMT, int GBN, int KW>
-__global__ __launch_bounds__(GBN * KW * 64, (GBN == 4 && KW == 1 && BM <= 128) ? 2 : 1) void gemm_kernel(
+__global__ __launch_bounds__(GBN * KW * 64, GBN == 4 && KW == 1 ? 2 : 1) void gemm_kernel(
     const uint16_t* __restrict__ X, int M, const u32x4* __restrict__ hi, const u32x4* __restrict__ lo,
     const uint16_t* __restrict__ scales, int N, int K, uint16_t* __restrict__ Y,
     float4v* __restrict__ partials, uint32_t* __restrict__ counters, int split_k, int gshift, int second_launch)
@@ -583,7 +583,7 @@ __global__ __launch_bounds__(256) void add_slices_kernel(const float4v* __restri
     *reinterpret_cast<half4*>(Y + (size_t)m * N + n) = to_out4<FMT>(yv);
 }
 
-template <int BM, int D, int DQ = kBiasShift, bool FGQ = false, int FMT = kE3M2, int GBN = 8, int KW = 1>
+template <int BM, int DQ = kBiasShift, bool FGQ = false, int FMT = kE3M2, int GBN = 8, int KW = 1>
 static hipError_t launch_gemm_t(const LinearPlan& p, const uint16_t* X, int64_t M, const void* hi, const void* lo,
                                 const uint16_t* scales, int64_t N, int64_t K, uint16_t* Y, void* workspace,
                                 hipStream_t stream)
@@ -592,6 +592,7 @@ static hipError_t launch_gemm_t(const LinearPlan& p, const uint16_t* X, int64_t 
     float4v* partials = reinterpret_cast<float4v*>(reinterpret_cast<char*>(workspace) + kZeroBytes);
     const int64_t mblk = (M + BM - 1) / BM, nblk = (N / kTile + GBN - 1) / GBN;
     const unsigned grid = (unsigned)(mblk * ((nblk * p.split_k + 7) / 8 * 8));   // padded: see the id mapping
+    constexpr int D = ring_stages(BM, GBN, KW);
     hipLaunchKernelGGL((gemm_kernel<BM, D, DQ, FGQ, FMT, GBN, KW>), dim3(grid), dim3(GBN * KW * 64), 0, stream, X, (int)M,
                        (const u32x4*)hi, (const u32x4*)lo, scales, (int)N, (int)K, Y, partials, counters, p.split_k, p.gshift, p.second_launch);
     if (p.second_launch) {

@@ -35,13 +35,22 @@ hipError_t launch_unpack_codes(int format, const void* hi, const void* lo, int64
 hipError_t launch_dequantize(int format, const void* hi, const void* lo, const uint16_t* scales, int64_t N, int64_t K,
                              int64_t block, uint16_t* W_hat, hipStream_t stream);
 
+// Tiled kernel: stages of the DMA ring of a workgroup.  Four-wavefront workgroups are built so that two fit a compute unit (at most 256
+// registers a lane and 80 KB of LDS), i.e. two wavefronts per SIMD as with eight-wavefront workgroups: 4 to 10 % faster than deeper
+// rings with one workgroup per unit.  Within that, four stages at 32 rows and three at 48 to 112 (2 to 7 % faster than two at 80 to 112; a
+// fourth at 48 is 1 % slower); eight wavefronts have four up to 64 rows and three above, two K-ways two (one more: no gain).
+constexpr int ring_stages(int block_m, int gbn, int kw)
+{
+    return kw == 2 ? 2 : gbn == 8 ? (block_m > 64 ? 3 : 4) : (block_m == 128 ? 2 : (block_m > 32 ? 3 : 4));
+}
+
 // A fully resolved launch plan for fp6_linear.
 struct LinearPlan {
     int variant;        // FP6_VARIANT_DECODE or FP6_VARIANT_GEMM
     int split_k;        // K-slices handled by separate workgroups (>= 1)
-    int block_m;        // GEMM: rows of X per workgroup (32, 48, 64, 80, 96, 112 or 128); DECODE: 16
+    int block_m;        // GEMM: rows of X per workgroup (32, 48, 64, 80, 96, 112 or 128); DECODE: 16, 32 or 64
     int waves;          // wavefronts per workgroup
-    int depth;          // tiles in the per-wavefront prefetch ring
+    int depth;          // DECODE: tiles in the per-wavefront prefetch ring; GEMM: ring_stages (what the kernel is built with)
     size_t partial_bytes;   // fp32 partial sums needed in the workspace (0 if split_k == 1)
     int counters;       // arrival counters used (0 if split_k == 1)
     int format;         // 6: FP6 E3M2 (4+2 planes); 5: FP5 E3M1 (4+1 planes)
