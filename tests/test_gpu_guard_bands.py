@@ -13,7 +13,8 @@ import paper_2312_08583_amd as P
 from paper_2312_08583_amd import binding as B
 from paper_2312_08583_amd import inputs
 
-from gpu_util import assert_y_close, oracle_reference
+from oracle import fp6_oracle as O
+from gpu_util import assert_y_close, oracle_reference, to_np16
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -80,6 +81,68 @@ def test_linear_writes_only_inside_its_buffers(M, N, K, variant, split):
         assert not ws.window[:zero].any(), "counters and slots are not left zero"
     _, _, Yref = oracle_reference(W, X)
     assert_y_close(Y, Yref, "banded buffers")
+
+
+# (format, M, N, K, rows a workgroup): automatic plans of the tiled kernel between the powers of two, where the groups of rows that the
+# wavefronts move wrap around, and of the streaming kernel with whole lines of X and several blocks of rows
+AUTO = [
+    ("fp6", 33, 16640, 1536, 48), ("fp6", 65, 20672, 3072, 80), ("fp6", 257, 12544, 192, 96), ("fp6", 203, 9344, 3072, 112),
+    ("fp5", 131, 27136, 256, 80), ("v2", 164, 20736, 256, 96), ("bf16", 533, 6272, 448, 112), ("fgq", 71, 20672, 320, 48),
+    ("fp6", 19, 192, 1152, 32), ("fp6", 35, 192, 1152, 64), ("fp5", 25, 704, 1088, 32), ("v2", 31, 1024, 4096, 32), ("bf16", 18, 16448, 704, 32),
+]
+
+
+@pytest.mark.parametrize("fmt,M,N,K,rows", AUTO)
+def test_automatic_plans_write_only_inside_their_buffers(fmt, M, N, K, rows):
+    block = 64 if fmt == "fgq" else 0
+    plan = P.fp6_linear_plan(M, N, K, format={"fp5": 5, "v2": 7, "bf16": 8}.get(fmt, 6), block=block)
+    assert plan["block_m"] == rows
+    dtype = torch.bfloat16 if fmt == "bf16" else torch.float16
+    W = inputs.weight(N, K, seed=1000 + N + K, sigma=0.02, outlier_frac=0.001, device=DEV)
+    X = (inputs.activation_bf16 if fmt == "bf16" else inputs.activation)(M, K, seed=1100 + M, device=DEV)
+    planes = P.fp6_quantize_pack_fgq(W, block) if block else {"fp6": P.fp6_quantize_pack, "fp5": P.fp5_quantize_pack}.get(
+        fmt, P.fp6_quantize_pack_v2)(W)
+    hi, lo, sc = (Banded(t.numel() * t.element_size(), t) for t in planes)
+    xb, yb, ws = Banded(2 * M * K, X), Banded(2 * M * N), Banded(max(plan["workspace_bytes"], 16))
+    yb.window.fill_(0xFF)                       # NaN patterns of either type: every element of Y must be overwritten
+    ws.window.zero_()
+    fn = {"fp6": P.fp6_linear, "fp5": P.fp5_linear, "v2": P.fp6_linear_v2, "bf16": P.fp6_linear_v2_bf16, "fgq": P.fp6_linear_fgq}[fmt]
+    Y = yb.view(dtype, (M, N))
+    for _ in range(2):
+        fn(xb.view(dtype, (M, K)), hi.window, lo.window, sc.view(torch.float16, planes[2].shape), N, K, *((block,) if block else ()),
+           out=Y, workspace=ws.window)
+    torch.cuda.synchronize()
+    for name, b in (("Y", yb), ("workspace", ws), ("hi_plane", hi), ("lo_plane", lo), ("scales", sc), ("X", xb)):
+        assert b.bands_intact(), "guard band of %s was written" % name
+    for b, t in zip((hi, lo, sc, xb), (*planes, X)):
+        assert torch.equal(b.window, t.contiguous().view(torch.uint8).reshape(-1)), "an input was modified"
+    if plan["workspace_bytes"]:
+        assert not ws.window[:B.FP6_WORKSPACE_ZERO_BYTES].any(), "counters and slots are not left zero"
+    assert not Y.isnan().any()
+    if fmt != "bf16":                           # (bf16 against the oracle: test_gpu_block_heights, test_gpu_stream_formats)
+        pick = torch.cat([torch.arange(64), torch.arange(N - 64, N)])
+        wb, x16 = to_np16(W[pick.to(DEV)].contiguous()), to_np16(X)
+        if fmt == "fgq":
+            Yref = O.linear_fgq(x16, *O.quantize_fgq(wb, block), block)
+        else:
+            Yref = (O.linear5 if fmt == "fp5" else O.linear)(x16, *(O.quantize5 if fmt == "fp5" else O.quantize)(wb))
+        assert_y_close(Y.cpu()[:, pick], Yref, (fmt, M, N, K))
+
+
+@pytest.mark.parametrize("fmt", ["fp5", "v2"])
+@pytest.mark.parametrize("N,K", [(192, 320), (64, 1088)])
+def test_dequantize_of_the_other_formats_writes_only_inside_its_buffer(fmt, N, K):
+    W = inputs.weight(N, K, seed=950 + N, sigma=0.02, outlier_frac=0.001, device=DEV)
+    planes = (P.fp5_quantize_pack if fmt == "fp5" else P.fp6_quantize_pack_v2)(W)
+    hi, lo, sc = (Banded(t.numel() * t.element_size(), t) for t in planes)
+    what = Banded(2 * N * K)
+    fn = getattr(B.lib(), "fp5_dequantize" if fmt == "fp5" else "fp6_dequantize_v2")
+    assert fn(hi.window.data_ptr(), lo.window.data_ptr(), sc.window.data_ptr(), N, K, what.window.data_ptr(),
+              torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    assert all(b.bands_intact() for b in (hi, lo, sc, what))
+    ref = (P.fp5_dequantize if fmt == "fp5" else P.fp6_dequantize_v2)(*planes, N, K)
+    assert torch.equal(what.view(torch.int16, (N, K)), ref.view(torch.int16))
 
 
 @pytest.mark.parametrize("N,K,block", [(192, 320, 0), (64, 4096, 0), (320, 512, 128)])
