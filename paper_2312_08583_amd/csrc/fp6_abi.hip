@@ -427,7 +427,7 @@ bool make_plan(int format, int64_t M, int64_t N, int64_t K, int64_t block, int v
         }
         // The rows of X are dealt evenly to as many workgroups as the plan has along M, in whole blocks of 16: the same grid and
         // the same sums, bit for bit, without most of the rows past M.  A plan of 64 rows runs with 48 or 64, one of 128 with
-        // 80 to 128.  Measured against blocks of 64 and 128 throughout, 150 random plans that this changes (M = 34 ... 784, all
+        // 80 to 128.  Measured against blocks of 64 and 128 throughout, 230 random plans that this changes (M = 34 ... 784, all
         // formats): 0.90 of the time, none slower (75 x 23872 x 9152 67.3 / 51.3 us, 333 x 13824 x 5120 in bf16 56.5 / 51.9;
         // 48 rows for 64 0.92 on the average).  The ablations have 32, 64 and 128 rows only.
         if (!hint_bm && !hint_dequant && p.block_m >= 64) {

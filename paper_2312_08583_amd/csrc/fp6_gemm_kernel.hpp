@@ -25,14 +25,15 @@
 // LDS traffic per k tile: every wavefront reads the whole X slice (wavefronts x BM x 128 B) plus its
 // planes - at BM = 128 about 152 KB per 2048 MFMA cycles of a SIMD, some 60 % of the 128 B/clk port.
 // What bounds it (cycle counter and wall clock read in the kernel, random data): with every compute unit busy the clock.  A
-// step at 128 x 512 takes 2450 cycles of the 2048 its MFMAs need, at 1.8 GHz (2048 x 8192 x 8192: 1.39 PFLOP/s); without the
-// LDS reads of X it takes 2410, without the DMA or without the unpack 2230, without all three 2070 - and the clock stays at
-// 1.8 to 2.0, where an MFMA-only loop on random operands settles too (1.98 PFLOP/s, 2.44 on zeros).  What costs energy costs
-// time there: 5, 11 and 12 %.  With 172 units busy (512 x 22016 x 8192) the clock is 2.2 GHz.  The vector operations of
-// the unpack hide behind the MFMAs of a SIMD's two wavefronts as long as there are no more than two of them to each, evenly spread:
-// in bursts they cost a quarter (a loop of nothing else: 2640 cycles against 2140).
+// step at 128 x 512 takes 2430 cycles of the 2048 its MFMAs need, at 1.84 GHz: 170 us for the 128 steps of 2048 x 8192 x 8192, 162 to
+// 175 by unit, in a call of 186 (1.48 PFLOP/s; 198 on a slower machine); the rest is 2.2 us of prologue, 3.8 of epilogue and 5 between
+// launches.  Without the LDS reads of X a step takes 40 cycles less, without the DMA or without the unpack 220, without all three 380 - and
+// the clock stays at 1.8 to 2.0, where an MFMA-only loop on random operands settles too (1.98 PFLOP/s, 2.44 on zeros).  What costs energy
+// costs time there: 5, 11 and 12 %.  With 172 units busy (512 x 22016 x 8192) the clock is 2.3 GHz, 2407 cycles a step and 135 us of 153.
+// The vector operations of the unpack hide behind the MFMAs of a SIMD's two wavefronts as long as there are no more than two of them to
+// each, evenly spread: in bursts they cost a quarter (a loop of nothing else: 2640 cycles against 2140).
 // Four-wavefront workgroups with a compute unit to themselves are bound by the instructions one wavefront can issue, one
-// in five cycles or so: 1190 cycles a step at 64 rows (210 instructions, 512 cycles of MFMAs).
+// in five cycles or so: 1190 cycles a step at 64 rows (210 instructions, 512 cycles of MFMAs), 1325 at 112 rows in bf16 (896).
 // Where K is split, the meeting of the slices costs another 5-12 % at M = 512.
 //
 // The row scale is applied once, after the accumulation (Section 5.2).  K may be split
@@ -251,9 +252,9 @@ __global__ __launch_bounds__(GBN * KW * 64, GBN == 4 && KW == 1 ? 2 : 1) void ge
     // weights is unpacked, and no two DMA instructions follow each other, which would keep the wavefront waiting.
     // The planes are a wavefront's own: it waits for its own DMA, and refills a stage once the next one has been read.  The
     // activations are everyone's: the barrier comes where the next step's are read first.
-    // Against reading a step's operands together behind its barrier, and unpacking each fragment in front of its MFMAs (us):
-    // 333 x 13824 x 5120 in bf16 65.1 -> 60.7, 512 x 8192 x 22016 157 -> 151, 198 random plans 4-5 % at 128 x 256, 2-3 % at
-    // 128 x 512 and 64 x 256.  At 32 rows (kWhole) a group has 29 vector operations to 4 MFMAs and nothing to hide; there
+    // Against reading a step's operands together behind its barrier, and unpacking each fragment in front of its MFMAs (us, planes of
+    // random bits, in turn): 333 x 13824 x 5120 in bf16 66.5 / 61.9 (blocks of 128 rows both), 512 x 8192 x 22016 159 / 144, 512 x 22016 x
+    // 8192 165 / 157, 2048 x 8192 x 8192 199 / 192; 198 random plans 4-5 % at 128 x 256, 2-3 % at 128 x 512 and 64 x 256.  At 32 rows (kWhole) a group has 29 vector operations to 4 MFMAs and nothing to hide; there
     // all operands are read a step ahead, behind the barrier at the step's head, and each fragment is unpacked where it is used.
     // tail < 0: a step of the steady state.  Otherwise the tail-th of the last steps, for which everything has been issued: the
     // loads that may be in flight are those of the steps after the next, and the D-th of them has no next step.

@@ -3,8 +3,8 @@
 // A call from Python took 10 us, of which the kernel of a small layer is 3: some thirty attribute reads and checks, a ctypes call with
 // eleven conversions and the look-up of the current stream.  With them here it takes 3.3 to 4.4, most of it the launch (1 x 1024 x 1024,
 // calls back to back 10.3 -> 4.7 us; the four calls of a 7B-shaped block at four rows 50 -> 39).  Whatever is not a plain call - a
-// missing workspace, a tensor subclass, an active function or dispatch mode, a wrapped tensor, an argument that does not fit - gets
-// None, and binding.py takes the call from there: it allocates, and it words the errors.
+// missing workspace, a tensor subclass, an active function or dispatch mode (torch.set_default_device installs one for good), a wrapped
+// tensor, an argument that does not fit - gets None, and binding.py takes the call from there: it allocates, and it words the errors.
 #include <Python.h>
 
 #include <ATen/ATen.h>
