@@ -652,7 +652,7 @@ static hipError_t launch_decode_half_t(const LinearPlan& p, const uint16_t* X, i
     return hipGetLastError();
 }
 
-// Which of the two forms of decode_block a launch takes.  Straight code for the last tiles needs registers (172 to 208 of a lane's
+// Which of the two forms of decode_block a launch takes.  Straight code for the last tiles needs registers (172 to 236 of a lane's
 // 512, 332 to 392 and 512 with two and four row blocks; the short form 104 to 136, 158 to 190 and 244): it is for launches whose workgroups
 // then still fit the chip at once, two to a compute unit or one.  With three tiles or less to a wavefront there is nothing but last tiles, and the code
 // of their number is fetched for one use.  Measured against one form for all, time by tiles to a wavefront: 2 1.04, 2 to 3 1.00, 3 to 4 0.95,
